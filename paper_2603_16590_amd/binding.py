@@ -98,7 +98,7 @@ class BatqError(RuntimeError):
 def _load() -> C.CDLL:
     if not os.path.exists(LIB_PATH):
         raise ImportError(
-            f"{LIB_PATH} is missing: build it with `python -m paper_2603_16590_amd.build` "
+            f"{LIB_PATH} is missing: build it with `python paper_2603_16590_amd/build.py` "
             "(there is no fallback path)")
     # The tensors this binding is handed live in torch's HIP runtime, and torch ships its own copy of it: that copy
     # has to be in the process before the library's dependency on the HIP runtime is resolved, or the library gets
