@@ -62,10 +62,15 @@ __device__ __forceinline__ void store8<uint16_t>(uint16_t* p, const float (&v)[8
     *reinterpret_cast<uint4*>(p) = o;
 }
 
-// One wave per (32-row tile, K group of 8 MX blocks): 4 (MXFP4) or 8 (MXFP8) pieces of 1 KiB.  Every lane
-// converts 8 elements at a time (4 or 8 code bytes -> one 16-byte store of bf16, two of fp32), and the lanes are
-// laid over a piece so that neighbours hold neighbouring elements of a row: one wave instruction reads
-// 256 (512) contiguous code bytes and writes 4 (8) rows x 256 (128) contiguous output bytes.
+// Bound: HBM (codes and scales in, 16 or 32 bits per element out), for a decode step's window (8192 x 1024) the
+// latency of one round of loads.  One wave per (16-row group, K group of 8 MX blocks): 2 (MXFP4) or 4 (MXFP8) pieces of
+// 1 KiB.  Every lane converts 8 elements at a time (4 or 8 code bytes -> one 16-byte store of bf16, two of fp32), and the
+// lanes are laid over a piece so that neighbours hold neighbouring elements of a row: one wave instruction reads
+// 256 (512) contiguous code bytes and writes 4 (8) rows x 256 (128) contiguous output bytes.  All codes of the unit and
+// the 8-byte scale words of its rows are requested before the first conversion: a scale byte fetched inside the window's
+// bounds check is a load the compiler has to wait for, one after the other, sixteen of them in units of 32 rows
+// (graph-replayed, 8-bit codes to bf16: 1024 x 1024 7.5 -> 3.9 us, 8192 x 1024 10.8 -> 8.0, 32768 x 1024 27.4 ->
+// 22.3; 4-bit 8192 x 1024 9.8 -> 6.6).  Rows outside the window take the scales of the nearest row inside and are not stored.
 // bf16 output uses the hardware converts (two codes -> two bf16, times 2^(scale byte - 127)); they are exact for
 // every result in bf16's normal range, smaller ones are not specified here.  fp32 output is computed as
 // code value x 2^(byte - 127), exact in fp32 (subnormals included; scale byte 255 and the E4M3 NaN codes give NaN).
@@ -73,43 +78,50 @@ template <typename OT, bool FP8>
 __global__ void __launch_bounds__(256)
 dequant_kernel(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales, int M, int nb, int row0,
                int srows, OT* __restrict__ out, int64_t ldo, bool big) {
-    constexpr int kPerRow = FP8 ? 4 : 2;                   // pieces of a K group per 16-row group
-    constexpr int kPieces = 2 * kPerRow;
+    constexpr int kPieces = FP8 ? 4 : 2;                   // of the K group in this 16-row group
     constexpr int kSub = FP8 ? 2 : 4;                       // wave instructions per piece
     constexpr int kRows = 16 / kSub;                        // piece rows per instruction
     constexpr bool kHw = sizeof(OT) == 2;                   // bf16 output
     const int lane = threadIdx.x & 63;
     const int groups = scale_groups(nb);
-    const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    // (a unit is at least 2 KiB of codes, so their number fits 32 bits)
+    const uint32_t unit = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     // rows row0 .. row0 + M - 1 of arrays laid out for srows rows -> out rows 0 .. M - 1
-    const int first_tile = row0 >> 5, last_tile = (row0 + M - 1) >> 5;
-    const int tile = first_tile + (int)(unit / groups), g = (int)(unit % groups);
-    if (tile > last_tile) return;                           // wave-uniform
+    const int first_rg = row0 >> 4, last_rg = (row0 + M - 1) >> 4;
+    const int rg = first_rg + (int)(unit / (uint32_t)groups), g = (int)(unit % (uint32_t)groups);
+    if (rg > last_rg) return;                               // wave-uniform
     const size_t stages = (size_t)(FP8 ? code8_stages(nb) : code_stages(nb));
     // this lane inside an instruction's rows: row, 16-byte slot of the row, 8-element part of the slot
     const int lr = FP8 ? lane >> 3 : lane >> 4;
     const int pos = FP8 ? (lane >> 1) & 3 : (lane >> 2) & 3;
     const int part = FP8 ? lane & 1 : lane & 3;
     uint2 w[kPieces][kSub];
-#pragma unroll
-    for (int p = 0; p < kPieces; ++p) {
-        const uint8_t* piece = codes + ((size_t)(2 * tile + p / kPerRow) * stages + (size_t)(g * kPerRow + p % kPerRow)) * 1024;
-#pragma unroll
-        for (int i = 0; i < kSub; ++i) {
-            if constexpr (FP8) w[p][i] = *reinterpret_cast<const uint2*>(piece + i * 512 + lane * 8);
-            else w[p][i] = uint2{*reinterpret_cast<const uint32_t*>(piece + i * 256 + lane * 4), 0u};
-        }
-    }
+    uint64_t sw[kSub];                                      // a row's 8 scale bytes: even blocks, then odd ones
+    const uint8_t* src = codes + ((size_t)rg * stages + (size_t)(g * kPieces)) * 1024;
 #pragma unroll
     for (int p = 0; p < kPieces; ++p)
 #pragma unroll
         for (int i = 0; i < kSub; ++i) {
-            const int r = i * kRows + lr;                   // row inside the piece
-            const int slot = pos ^ ((r >> 2) & 3);          // undo the bank swizzle
-            const int row = tile * 32 + (p / kPerRow) * 16 + r;
-            const int k = g * 8 + (p % kPerRow) * (FP8 ? 2 : 4) + (FP8 ? slot >> 1 : slot);
-            if (row < row0 || row >= row0 + M || k >= nb) continue;
-            const uint32_t byte = scales[scale_index_internal(row, k, srows)];
+            if constexpr (FP8) w[p][i] = *reinterpret_cast<const uint2*>(src + p * 1024 + i * 512 + lane * 8);
+            else w[p][i] = uint2{*reinterpret_cast<const uint32_t*>(src + p * 1024 + i * 256 + lane * 4), 0u};
+        }
+#pragma unroll
+    for (int i = 0; i < kSub; ++i) {
+        const int row = min(max(rg * 16 + i * kRows + lr, row0), row0 + M - 1);
+        sw[i] = *reinterpret_cast<const uint64_t*>(scales + ((size_t)g * srows + row) * 8);
+    }
+#pragma unroll
+    for (int i = 0; i < kSub; ++i) {
+        const int r = i * kRows + lr;                       // row inside the group
+        const int row = rg * 16 + r;
+        const int slot = pos ^ ((r >> 2) & 3);              // undo the bank swizzle
+        const bool live = row >= row0 && row < row0 + M;
+#pragma unroll
+        for (int p = 0; p < kPieces; ++p) {
+            const int kk = p * (FP8 ? 2 : 4) + (FP8 ? slot >> 1 : slot);      // block inside the K group
+            const int k = g * 8 + kk;
+            if (!live || k >= nb) continue;
+            const uint32_t byte = (uint32_t)(sw[i] >> (8 * (kk >> 1) + 32 * (kk & 1))) & 0xFFu;
             OT* o = out + (size_t)(row - row0) * ldo + (size_t)k * 32 + (FP8 ? (slot & 1) * 16 + part * 8 : part * 8);
             const uint2 d = w[p][i];
             if constexpr (kHw) {
@@ -142,6 +154,7 @@ dequant_kernel(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ sc
                 store8<OT>(o, v);
             }
         }
+    }
 }
 
 template <typename XT>
@@ -378,8 +391,8 @@ hipError_t apply_typed(const batq_transform* t, const XT* X, int M, int64_t ldx,
 hipError_t launch_dequantize(const uint8_t* codes, const uint8_t* scales, int M, int nb, bool fp8, void* out,
                              batq_dtype odtype, int64_t ldo, int row_offset, int layout_rows, hipStream_t stream) {
     if (M == 0) return hipSuccess;
-    const int tiles = ((row_offset + M - 1) >> 5) - (row_offset >> 5) + 1;
-    const int64_t units = (int64_t)tiles * scale_groups(nb);                // one wave each, four to a workgroup
+    const int row_groups = ((row_offset + M - 1) >> 4) - (row_offset >> 4) + 1;
+    const int64_t units = (int64_t)row_groups * scale_groups(nb);           // one wave each, four to a workgroup
     const dim3 grid((unsigned)((units + 3) / 4)), block(256);
     const bool big = (size_t)M * nb * 32 * (odtype == BATQ_BF16 ? 2 : 4) > (size_t(128) << 20);
     if (odtype == BATQ_BF16) {

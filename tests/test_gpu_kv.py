@@ -298,3 +298,25 @@ def test_cache_filled_by_appends_equals_one_call(B, bits, form, dtype):
     outp = torch.zeros((4, K), device="cuda")
     assert lib.batq_kv_dequantize(codes.data_ptr(), scales.data_ptr(), cap, cap - 3, 4, K, bits, outp.data_ptr(), 0, K,
                                   None) == 2
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("K", [32, 288, 1024])
+def test_window_edges_of_the_dequantiser(B, bits, K):
+    """Windows that start or end at, just before and just after a 16-row code group, read from arrays laid out for a
+    ragged row count: the rows of the whole-array result, exactly, and nothing written around them (columns past K, rows
+    past the window)."""
+    import torch
+    cap = 75
+    gen = torch.Generator(device="cuda").manual_seed(K + bits)
+    n = B.batq_code8_bytes(cap, K) if bits == 8 else B.batq_code_bytes(cap, K)
+    codes = torch.randint(0, 120, (n,), dtype=torch.uint8, device="cuda", generator=gen)
+    scales = torch.randint(120, 135, (B.batq_scale_bytes(cap, K),), dtype=torch.uint8, device="cuda", generator=gen)
+    for dtype in (torch.bfloat16, torch.float32):
+        ref = B.batq_dequantize(codes, scales, cap, K, bits, out_dtype=dtype)
+        for row0, m in ((0, 1), (0, 16), (0, 17), (15, 1), (15, 2), (16, 16), (17, 31), (31, 33), (64, 11), (74, 1), (0, 75)):
+            wide = torch.full((m + 2, K + 8), 7.0, dtype=dtype, device="cuda")
+            B.batq_kv_dequantize(codes, scales, cap, row0, m, K, bits, out=wide[:m, :K])
+            torch.cuda.synchronize()
+            assert torch.equal(wide[:m, :K], ref[row0:row0 + m]), (row0, m)
+            assert bool((wide[:, K:] == 7.0).all()) and bool((wide[m:] == 7.0).all()), (row0, m)
