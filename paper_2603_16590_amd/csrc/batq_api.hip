@@ -146,6 +146,8 @@ void free_transform(batq_transform* t) {
     if (t->d_clip) (void)hipFree(t->d_clip);
     if (t->d_clip_max) (void)hipFree(t->d_clip_max);
     if (t->d_Tinv) (void)hipFree(t->d_Tinv);
+    if (t->d_outer_inv) (void)hipFree(t->d_outer_inv);
+    if (t->d_inner_inv) (void)hipFree(t->d_inner_inv);
     if (t->d_Tf64) (void)hipFree(t->d_Tf64);
     if (t->d_Tsplit) (void)hipFree(t->d_Tsplit);
     if (t->d_TinvSplit) (void)hipFree(t->d_TinvSplit);
@@ -156,7 +158,6 @@ void free_transform(batq_transform* t) {
 void free_weight(batq_weight* w) {
     if (!w) return;
     if (w->d_codes) (void)hipFree(w->d_codes);
-    if (w->d_scales) (void)hipFree(w->d_scales);
     delete w;
 }
 
@@ -180,12 +181,15 @@ batq_status alloc_weight(batq_weight** out, int K, int N) {
         void* unused = nullptr;                             // first use of the device: resolve the static scratch array
         if (batq::static_scratch(&unused) != hipSuccess) (void)hipGetLastError();
     }
-    if (hipMalloc(reinterpret_cast<void**>(&w->d_codes), batq::code_bytes_blocked(N, K / 32)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&w->d_scales), batq::scale_bytes_internal(N, K / 32)) != hipSuccess) {
+    // one allocation for both arrays: allocating and freeing a large block cost ~11 us each
+    const size_t code_bytes = batq::code_bytes_blocked(N, K / 32);          // a multiple of 1 KiB
+    if (hipMalloc(reinterpret_cast<void**>(&w->d_codes), code_bytes + batq::scale_bytes_internal(N, K / 32)) != hipSuccess) {
         (void)hipGetLastError();
+        w->d_codes = nullptr;
         free_weight(w);
         return BATQ_ERR_ALLOC;
     }
+    w->d_scales = w->d_codes + code_bytes;
     *out = w;
     return BATQ_OK;
 }
@@ -234,7 +238,7 @@ batq_status batq_transform_create_ex(batq_transform** out, const batq_transform_
     // host fp64: the dense forward blocks T_k, their inverses (from the inverted factors for the
     // Kronecker forms, T_k^-1 = O_k^-1 (x) I_k^-1), and T_k split into three bf16 terms in the lane
     // order of the activation kernel's matrix-instruction operand
-    std::vector<double> T, Tinv;
+    std::vector<double> T, Tinv, outer_inv, inner_inv;
     std::vector<float> Tf;
     std::vector<uint16_t> Tsplit, TinvSplit, TinvTSplit;
     if (form != BATQ_FORM_IDENTITY) {
@@ -248,10 +252,12 @@ batq_status batq_transform_create_ex(batq_transform** out, const batq_transform_
                 if (k == 0 || d->outer_per_block) {
                     for (int i = 0; i < go * go; ++i) Od[i] = O[i];
                     if (!invert_small(Od.data(), go, Oinv.data())) return BATQ_ERR_SINGULAR;
+                    outer_inv.insert(outer_inv.end(), Oinv.begin(), Oinv.end());
                 }
                 if (k == 0 || d->inner_per_block) {
                     for (int i = 0; i < gi * gi; ++i) Id[i] = I[i];
                     if (!invert_small(Id.data(), gi, Iinv.data())) return BATQ_ERR_SINGULAR;
+                    inner_inv.insert(inner_inv.end(), Iinv.begin(), Iinv.end());
                 }
                 double* Tk = T.data() + (size_t)k * 1024;
                 double* Tik = Tinv.data() + (size_t)k * 1024;
@@ -296,6 +302,8 @@ batq_status batq_transform_create_ex(batq_transform** out, const batq_transform_
         t->inner_stride = d->inner_per_block ? gi * gi : 0;
         st = upload(&t->d_outer, d->outer, (size_t)(d->outer_per_block ? nb : 1) * go * go);
         if (st == BATQ_OK) st = upload(&t->d_inner, d->inner, (size_t)(d->inner_per_block ? nb : 1) * gi * gi);
+        if (st == BATQ_OK) st = upload(&t->d_outer_inv, outer_inv.data(), outer_inv.size());
+        if (st == BATQ_OK) st = upload(&t->d_inner_inv, inner_inv.data(), inner_inv.size());
     }
     if (st == BATQ_OK && form == BATQ_FORM_DENSE) st = upload(&t->d_T, Tf.data(), Tf.size());
     if (st == BATQ_OK && t->has_transform) {
@@ -376,12 +384,8 @@ batq_status prepare_weight_impl(batq_weight** out, const batq_transform* t, cons
         free_weight(w);
         return st;
     }
-    // padding: zero codes (rows up to a multiple of 16, K up to a multiple of 256), neutral scales
-    hipError_t e = hipMemsetAsync(w->d_scales, 127, batq::scale_bytes_internal(N_out, nb), s);
-    if (e == hipSuccess) e = hipMemsetAsync(w->d_codes, 0, batq::code_bytes_blocked(N_out, nb), s);
-    if (e == hipSuccess)
-        e = batq::launch_prepare_weight(t, W, wdtype, K, N, ldw, w_is_KxN, N_out, W_up ? 0 : -1, d_clip_a, d_clip_b,
-                                        w->d_codes, w->d_scales, s);
+    hipError_t e = batq::launch_prepare_weight(t, W, wdtype, K, N, ldw, w_is_KxN, N_out, W_up ? 0 : -1, d_clip_a,
+                                               d_clip_b, w->d_codes, w->d_scales, s);
     if (e == hipSuccess && W_up)
         e = batq::launch_prepare_weight(t, W_up, wdtype, K, N, ldw, w_is_KxN, N_out, 32, d_clip_a, d_clip_b,
                                         w->d_codes, w->d_scales, s);
@@ -422,8 +426,7 @@ batq_status batq_prepare_weight_minmax(batq_weight** out, const batq_transform* 
 batq_status batq_weight_export(const batq_weight* w, uint8_t* codes, uint8_t* scales, void* stream) {
     if (!w || !codes || !scales) return BATQ_ERR_NULL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    BATQ_HIP(batq::launch_codes_to_rowmajor(w->d_codes, codes, w->N, w->nb, s));
-    BATQ_HIP(batq::launch_scales_to_canonical(w->d_scales, scales, w->N, w->nb, s));
+    BATQ_HIP(batq::launch_weight_to_rowmajor(w->d_codes, w->d_scales, codes, scales, w->N, w->nb, s));
     return BATQ_OK;
 }
 

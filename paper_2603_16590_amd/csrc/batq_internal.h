@@ -27,6 +27,8 @@ struct batq_transform {
     float* d_clip = nullptr;      // [nb], 1.0 when no clipping
     float* d_clip_max = nullptr;  // [nb], only when minmax
     double* d_Tinv = nullptr;     // [nb][32][32] fp64 T_k^-1     (null when !has_transform)
+    double* d_outer_inv = nullptr;   // Kronecker forms: fp64 inverses of the factors, laid out as d_outer / d_inner
+    double* d_inner_inv = nullptr;
     double* d_Tf64 = nullptr;     // [nb][32][32] fp64 T_k        (null when !has_transform)
     uint16_t* d_Tsplit = nullptr; // [nb][3][2][64][8] bf16 three-term split of T_k in MFMA operand order
     uint16_t* d_TinvSplit = nullptr;   // the same split of T_k^-1
@@ -38,7 +40,7 @@ struct batq_weight {
     int K = 0, N = 0, nb = 0;
     int cus = 0;                  // compute units of the device the weight lives on
     uint8_t* d_codes = nullptr;   // blocked code layout (code_layout.h), rows and K zero-padded
-    uint8_t* d_scales = nullptr;  // internal group-major layout (scale_layout.h), padded groups
+    uint8_t* d_scales = nullptr;  // internal group-major layout (scale_layout.h), padded groups; same allocation as the codes
 };
 
 namespace batq {
@@ -94,7 +96,7 @@ hipError_t launch_prepare_weight(const batq_transform* t, const void* W, batq_dt
 // N_out / il_off: rows of the prepared weight and the interleave offset (-1: column n -> row n; 0 / 32: gate /
 // up columns of an MLP interleaved in groups of 32, N_out = 2 N).
 // d_clip_w_max != null selects the two-ratio clipping (d_clip_w then holds the ratios on the minimum).
-// Weight scales are written in the internal layout (pad bytes must have been set to 127).
+// Codes and scales are written whole, padding included (zero codes, neutral scales).
 // xscales_internal: activation scales in the grouped layout.
 // glu: gated output, Y = silu(gate) * up is M x N/2 for a weight with interleaved gate / up columns
 // (gemm_glu_supported says whether the shapes allow it).
@@ -117,6 +119,8 @@ int tile_schedule(int M, int N, int K, int compute_units, bool glu, bool allow_k
 hipError_t launch_codes8_to_blocked(const uint8_t* rowmajor, uint8_t* blocked, int rows, int nb, hipStream_t stream);
 hipError_t launch_codes8_to_rowmajor(const uint8_t* blocked, uint8_t* rowmajor, int rows, int nb, hipStream_t stream);
 hipError_t launch_codes_to_blocked(const uint8_t* rowmajor, uint8_t* blocked, int rows, int nb, hipStream_t stream);
+hipError_t launch_weight_to_rowmajor(const uint8_t* blocked, const uint8_t* internal, uint8_t* rowmajor, uint8_t* canon,
+                                     int rows, int nb, hipStream_t stream);
 hipError_t launch_codes_to_rowmajor(const uint8_t* blocked, uint8_t* rowmajor, int rows, int nb, hipStream_t stream);
 hipError_t launch_scales_to_internal(const uint8_t* canon, uint8_t* internal, int rows, int nb, hipStream_t stream);
 hipError_t launch_scales_to_canonical(const uint8_t* internal, uint8_t* canon, int rows, int nb, hipStream_t stream);

@@ -109,6 +109,23 @@ codes_to_rowmajor(const uint8_t* __restrict__ blocked, uint8_t* __restrict__ row
     }
 }
 
+// Codes and scales of a prepared weight to row-major order in one launch: the chunk of block k of a row and its scale byte
+// (4096 x 14336: 10.2 + 4.3 us and a launch gap as two kernels).
+__global__ void __launch_bounds__(256)
+weight_to_rowmajor(const uint8_t* __restrict__ blocked, const uint8_t* __restrict__ internal, uint8_t* __restrict__ rowmajor,
+                   uint8_t* __restrict__ canon, int rows, int nb) {
+    const size_t total = (size_t)rows * nb;
+    const bool narrow = total < (size_t(1) << 32);          // kernel-uniform: 32-bit division where it fits
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
+        const int row = narrow ? (int)((uint32_t)i / (uint32_t)nb) : (int)(i / nb);
+        const int k = (int)(i - (size_t)row * nb);
+        const uint4 v = *reinterpret_cast<const uint4*>(blocked + code_chunk_offset(row, k, nb));
+        const uint8_t s = internal[scale_index_internal(row, k, rows)];
+        *reinterpret_cast<uint4*>(rowmajor + i * 16) = v;
+        canon[i] = s;
+    }
+}
+
 // 8-bit codes: row-major [rows][nb*32]  <->  blocked 8-bit layout (one thread per 16-byte slot)
 __global__ void __launch_bounds__(256)
 codes8_to_blocked(const uint8_t* __restrict__ rowmajor, uint8_t* __restrict__ blocked, int rows, int nb) {
@@ -1818,6 +1835,14 @@ hipError_t launch_codes_to_rowmajor(const uint8_t* blocked, uint8_t* rowmajor, i
     const size_t total = (size_t)rows * nb;
     const int grid = (int)std::min<size_t>((total + 255) / 256, 8192);
     codes_to_rowmajor<<<grid, 256, 0, stream>>>(blocked, rowmajor, rows, nb);
+    return hipGetLastError();
+}
+
+hipError_t launch_weight_to_rowmajor(const uint8_t* blocked, const uint8_t* internal, uint8_t* rowmajor, uint8_t* canon,
+                                     int rows, int nb, hipStream_t stream) {
+    const size_t total = (size_t)rows * nb;
+    const int grid = (int)std::min<size_t>((total + 255) / 256, 8192);
+    weight_to_rowmajor<<<grid, 256, 0, stream>>>(blocked, internal, rowmajor, canon, rows, nb);
     return hipGetLastError();
 }
 

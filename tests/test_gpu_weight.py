@@ -87,6 +87,55 @@ def test_layouts_clip_and_dtypes(B):
     assert np.array_equal(gc, oc) and np.array_equal(gs, os_)
 
 
+@pytest.mark.parametrize("form", ["kron4", "kron8", "dense", "identity"])
+@pytest.mark.parametrize("K,N", [(32, 1), (96, 33), (288, 257)])
+def test_forms_storages_and_padding(B, form, K, N):
+    """Every form from both storages (16-byte aligned rows or not) on edges of the kernel's tiles, and the padding it
+    writes: a product with the weight reads whole K groups and row groups, so leftovers of the previous owner of the
+    memory would show in it."""
+    import torch
+    rng = np.random.default_rng(K + N)
+    nb = K // 32
+    if form == "kron4" or form == "kron8":
+        go, gi = (4, 8) if form == "kron4" else (8, 4)
+        G = (np.eye(go) + 0.05 * rng.standard_normal((go, go))).astype(np.float32)
+        P = (np.eye(gi) + 0.05 * rng.standard_normal((nb, gi, gi))).astype(np.float32)
+        T = o.kron_blocks(G, P)
+        t = B.Transform(K, G, P, None, g_outer=go, g_inner=gi)
+    elif form == "dense":
+        T = (np.eye(32) + 0.05 * rng.standard_normal((nb, 32, 32))).astype(np.float32)
+        t = B.Transform.general(K, dense=T)
+    else:
+        T = None
+        t = B.Transform(K, None, None, None)
+    W = bi.bf16_bits_to_f32(bi.f32_to_bf16_bits((0.02 * rng.standard_normal((K, N))).astype(np.float32)))
+    oc, os_ = o.prepare_weight_blocks(W, T) if T is not None else o.prepare_weight(W, None, None)
+    X = torch.from_numpy(rng.standard_normal((3, K)).astype(np.float32)).cuda()
+    xc, xs = B.batq_quantize_act(B.Transform(K, None, None, None), X)
+    rmx = B.batq_codes_to_rowmajor(xc, 3, K).cpu().numpy(), B.batq_scales_to_rowmajor(xs, 3, K).cpu().numpy()
+    junk = torch.full((64, K), 0xEE, dtype=torch.uint8, device="cuda")
+    for dtype in (torch.float32, torch.bfloat16):
+        Wd = torch.from_numpy(W).cuda().to(dtype)
+        pitch = (N + 15) // 8 * 8 + 1                                   # odd row pitch
+        wide = torch.zeros((K, pitch), dtype=dtype, device="cuda")
+        wide[:, :N] = Wd
+        tall = torch.zeros((N, K + 1), dtype=dtype, device="cuda")      # rows that are not 16-byte aligned
+        tall[:, :K] = Wd.t()
+        for M_, kxn in ((Wd, True), (wide[:, :N], True), (Wd.t().contiguous(), False), (tall[:, :K], False)):
+            # the allocator hands a freed block out again: fill one of about this size with other bytes first
+            B.batq_weight_import(junk.repeat((N + 63) // 64, 1)[:N, :K // 2].contiguous(),
+                                 junk.repeat((N + 63) // 64, 1)[:N, :nb].contiguous(), K, N).close()
+            if M_.stride(0) < M_.shape[1] or M_.stride(1) != 1:          # (a single column or row loses its pitch)
+                continue
+            wh = B.batq_prepare_weight(t, M_, kxn)
+            gc, gs = _export(B, wh)
+            _compare(gc, gs, oc, os_, tol=0)
+            Y = B.batq_gemm_mxfp4(xc, xs, wh, 3)
+            torch.cuda.synchronize()
+            ref = o.gemm(*rmx, gc, gs)
+            assert np.allclose(Y.cpu().numpy(), ref, rtol=1e-6, atol=1e-6 * np.abs(ref).max())
+
+
 def test_import_export_round_trip(B):
     import torch
     rng = np.random.default_rng(3)
