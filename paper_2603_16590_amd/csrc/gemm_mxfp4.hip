@@ -15,7 +15,8 @@
 //                 and the shares of one XCD form a compact block for its L2.  8 waves (two per SIMD)
 //                 where the tiles are three or four strips wide.
 //   gemm_mid    - few rows and strips: one 128 x 64 tile (and K part) per workgroup, at most one
-//                 workgroup per compute unit; X fragments straight from the L2 to registers.
+//                 workgroup per compute unit; X fragments straight from the L2 to registers.  4- and 8-bit X, plain and
+//                 gated output.
 //   gemm_direct - one wave per 32x32 tile with operands straight from global memory; only for
 //                 operand arrays of 2 GiB or more (the other kernels use 32-bit load offsets).
 #include <algorithm>
@@ -1005,8 +1006,11 @@ gemm_tiled(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const
 // (4 KiB per strip and stage, read by all four waves) go through LDS, each wave fetching one of a strip's four
 // 1 KiB pieces: with one strip, per stage 12 KiB enter the compute unit and 8 KiB of fragments are read from LDS,
 // against 20 KiB and 40 KiB for a 256 x 64 tile of the tiled kernel.
+// A8: MXFP8 activations; an X fragment is then two 16-byte loads (64-byte rows, both halves of both blocks of a K step), a
+// stage still 128 elements.  The 256-row tiles of gemm_tiled_a8 leave most compute units idle at these shapes (1024 x 14336 x
+// 4096: 83.3 us, here 58.5).  GLU: gated output; a strip is the 32 gate and the 32 up columns of the same outputs.
 //
-// Loads of a wave complete in the order it issued them.  Stage q's are: NS strip pieces, 2 RT fragments of X
+// Loads of a wave complete in the order it issued them.  Stage q's are: NS strip pieces, 2 RT (A8: 4 RT) fragments of X
 // and, for even q, RT + 2 NS scale dwords (those of the K group q opens); stages are issued in order.  At the top
 // of stage s a wave waits until only loads of the stages after s + 1 can be outstanding, then meets the others at
 // the barrier: the whole strip stage s + 1 is in LDS and is read to registers under the matrix instructions of
@@ -1017,11 +1021,12 @@ constexpr int kMidStripLds = 64 * kStageBytes;      // 4 KiB: one stage of one 6
                                                     // stages of its NS strips in LDS (a wave works D - 2 stages
                                                     // ahead); the epilogue's staging reuses them
 
-template <int RT, int D, int NS>
+template <int RT, int D, int NS, bool A8>
 struct MidCtx {
     static_assert(D % 2 == 0 && D >= 4, "stages come in K groups of two");
     static constexpr int NJ = 2 * NS;           // 32-column matrix tiles of a wave
-    uint32_t aoff[RT][2], boff[NS], sao[RT], sbo[NJ], lds0;
+    static constexpr int NA = A8 ? 4 : 2;       // 16-byte X loads of a lane, row tile and stage (8-bit: two per K step)
+    uint32_t aoff[RT][NA], boff[NS], sao[RT], sbo[NJ], lds0;
     int wave, T;
     // the next stage to load: its index, where its codes and the scales of its K group start
     int q;
@@ -1038,7 +1043,7 @@ struct MidCtx {
     // and the clamped pointer steps (a dozen scalar and vector instructions per stage, in a loop whose pace is set by
     // the instructions a wave issues) are left out.
     template <bool EVEN, bool LIVE = false>
-    __device__ __forceinline__ void issue(int slot, batq_u32x4 (&a)[RT][2], int (&sa)[RT], int (&sb)[NJ]) {
+    __device__ __forceinline__ void issue(int slot, batq_u32x4 (&a)[RT][NA], int (&sa)[RT], int (&sb)[NJ]) {
         if constexpr (LIVE) {
 #pragma unroll
             for (int n = 0; n < NS; ++n)
@@ -1046,7 +1051,7 @@ struct MidCtx {
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) load16_async(a[i][h], xq, aoff[i][h]);
+                for (int h = 0; h < NA; ++h) load16_async(a[i][h], xq, aoff[i][h]);
             if constexpr (EVEN) {
 #pragma unroll
                 for (int i = 0; i < RT; ++i) load4_async(sa[i], sag, sao[i]);
@@ -1054,7 +1059,7 @@ struct MidCtx {
                 for (int j = 0; j < NJ; ++j) load4_async(sb[j], sbg, sbo[j]);
             }
             ++q;
-            xq += 1024;
+            xq += NA * 512;
             wq += 1024;
             if constexpr (!EVEN) {
                 sag += sa_step;
@@ -1069,7 +1074,7 @@ struct MidCtx {
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) load16_async(a[i][h], xq, aoff[i][h] & m);
+            for (int h = 0; h < NA; ++h) load16_async(a[i][h], xq, aoff[i][h] & m);
         if constexpr (EVEN) {
 #pragma unroll
             for (int i = 0; i < RT; ++i) load4_async(sa[i], sag, sao[i] & m);
@@ -1078,7 +1083,7 @@ struct MidCtx {
         }
         ++q;
         const bool more = q < T;                      // uniform; the pointers stay on the last stage otherwise
-        xq += more ? 1024 : 0;
+        xq += more ? NA * 512 : 0;
         wq += more ? 1024 : 0;
         if constexpr (!EVEN) {
             sag += more ? sa_step : 0;
@@ -1086,16 +1091,16 @@ struct MidCtx {
         }
     }
     // loads a wave issues for a stage of parity p
-    static constexpr __device__ int count(int p) { return NS + 2 * RT + ((p & 1) == 0 ? RT + NJ : 0); }
+    static constexpr __device__ int count(int p) { return NS + NA * RT + ((p & 1) == 0 ? RT + NJ : 0); }
 };
 
 // Loads of stage indices Q .. D - 2, before the first stage is multiplied.
-template <int RT, int D, int NS, int Q>
-__device__ __forceinline__ void mid_prologue(MidCtx<RT, D, NS>& c, batq_u32x4 (&a)[D][RT][2], int (&sa)[D / 2][RT],
+template <int RT, int D, int NS, bool A8, int Q>
+__device__ __forceinline__ void mid_prologue(MidCtx<RT, D, NS, A8>& c, batq_u32x4 (&a)[D][RT][A8 ? 4 : 2], int (&sa)[D / 2][RT],
                                              int (&sb)[D / 2][2 * NS]) {
     if constexpr (Q < D - 1) {
         c.template issue<(Q & 1) == 0>(Q, a[Q], sa[Q >> 1], sb[Q >> 1]);
-        mid_prologue<RT, D, NS, Q + 1>(c, a, sa, sb);
+        mid_prologue<RT, D, NS, A8, Q + 1>(c, a, sa, sb);
     }
 }
 
@@ -1110,15 +1115,22 @@ __device__ __forceinline__ void mid_read_strips(const uint8_t* smem, int slot, i
     }
 }
 
+// Matrix instruction of K step H of a stage of parity PAR.
+template <bool A8, int PAR, int H>
+__device__ __forceinline__ void mid_mfma(v16f& acc, const batq_u32x4 (&a)[A8 ? 4 : 2], const uint4& b, int sa, int sb) {
+    if constexpr (A8) acc = mx_mfma<true, 2 * PAR + H>(frag8(as_uint4(a[2 * H]), as_uint4(a[2 * H + 1])), frag(b), acc, sa, sb);
+    else acc = mx_mfma<false, 2 * PAR + H>(frag(as_uint4(a[H])), frag(b), acc, sa, sb);
+}
+
 // Stages base + U .. base + D - 1 of a K part (base a multiple of D, so stage base + U lives in LDS
 // slot and register slot U and has parity U % 2).  ALL: all of them exist.  On entry b[U % 2] holds the strip
 // fragments of stage base + U; those of the next stage are read under its matrix instructions.
 // LIVE: the stages base + D - 1 .. base + 2 D - 2 whose loads are issued here exist and are not the last one.
-template <int RT, int D, int NS, int U, bool ALL, bool LIVE = false>
-__device__ __forceinline__ void mid_steps(MidCtx<RT, D, NS>& c, int base, const uint8_t* smem, int b_rd0, int b_rd1,
-                                          v16f (&acc)[RT][2 * NS], batq_u32x4 (&a)[D][RT][2],
+template <int RT, int D, int NS, bool A8, int U, bool ALL, bool LIVE = false>
+__device__ __forceinline__ void mid_steps(MidCtx<RT, D, NS, A8>& c, int base, const uint8_t* smem, int b_rd0, int b_rd1,
+                                          v16f (&acc)[RT][2 * NS], batq_u32x4 (&a)[D][RT][A8 ? 4 : 2],
                                           int (&sa)[D / 2][RT], int (&sb)[D / 2][2 * NS], uint4 (&b)[2][2 * NS][2]) {
-    using Ctx = MidCtx<RT, D, NS>;
+    using Ctx = MidCtx<RT, D, NS, A8>;
     constexpr int NJ = 2 * NS;
     if constexpr (U < D) {
         const int s = base + U;
@@ -1131,8 +1143,8 @@ __device__ __forceinline__ void mid_steps(MidCtx<RT, D, NS>& c, int base, const 
         constexpr int u1 = (U + 1) % D;
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
-            ready(a[u1][i][0]);
-            ready(a[u1][i][1]);
+#pragma unroll
+            for (int h = 0; h < Ctx::NA; ++h) ready(a[u1][i][h]);
             if constexpr ((u1 & 1) == 0) ready(sa[u1 >> 1][i]);
         }
         if constexpr ((u1 & 1) == 0) {
@@ -1148,13 +1160,11 @@ __device__ __forceinline__ void mid_steps(MidCtx<RT, D, NS>& c, int base, const 
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    mfma_one<2 * (U & 1), false>(acc[i][j], as_uint4(a[U][i][0]), b[U & 1][j][0], sa[U >> 1][i], sb[U >> 1][j]);
+                for (int j = 0; j < NJ; ++j) mid_mfma<A8, U & 1, 0>(acc[i][j], a[U][i], b[U & 1][j][0], sa[U >> 1][i], sb[U >> 1][j]);
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    mfma_one<2 * (U & 1) + 1, false>(acc[i][j], as_uint4(a[U][i][1]), b[U & 1][j][1], sa[U >> 1][i], sb[U >> 1][j]);
+                for (int j = 0; j < NJ; ++j) mid_mfma<A8, U & 1, 1>(acc[i][j], a[U][i], b[U & 1][j][1], sa[U >> 1][i], sb[U >> 1][j]);
         }
         // Every wave has read the fragments of stage s - 1 and finished its matrix instructions on them: the LDS
         // slot and registers of stage s - 1 take stage s + D - 1.  (After this stage's matrix instructions: for odd
@@ -1162,15 +1172,15 @@ __device__ __forceinline__ void mid_steps(MidCtx<RT, D, NS>& c, int base, const 
         constexpr int un = (U + D - 1) % D;
         c.template issue<(un & 1) == 0, LIVE>(un, a[un], sa[un >> 1], sb[un >> 1]);
         __builtin_amdgcn_sched_barrier(0);
-        mid_steps<RT, D, NS, U + 1, ALL, LIVE>(c, base, smem, b_rd0, b_rd1, acc, a, sa, sb, b);
+        mid_steps<RT, D, NS, A8, U + 1, ALL, LIVE>(c, base, smem, b_rd0, b_rd1, acc, a, sa, sb, b);
     }
 }
 
 // Requires operand code arrays below 2 GiB (32-bit load offsets).  Grid: (groups of NS strips, row panels of 128 RT,
 // K parts); YT = partial_f32: partial sums of K part blockIdx.z in store_partial order (ldy = 32-column blocks of the
 // padded output, part_stride = floats of a part).
-template <typename YT, int RT, int D, int NS>
-__global__ void __launch_bounds__(256, 2)
+template <typename YT, int RT, int D, int NS, bool A8, bool GLU>
+__global__ void __launch_bounds__(256, A8 && NS == 2 ? 1 : 2)
 gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const uint8_t* __restrict__ wc,
          const uint8_t* __restrict__ ws, int M, int N, int nb, int ksplit, YT* __restrict__ Y, int64_t ldy,
          int64_t part_stride) {
@@ -1193,26 +1203,29 @@ gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const u
     }
     const int T = 2 * t.ng;                                     // stages of 128 K elements
 
-    MidCtx<RT, D, NS> c;
+    using Ctx = MidCtx<RT, D, NS, A8>;
+    Ctx c;
     c.wave = wave;
     c.T = T;
     c.q = 0;
-    c.xq = xc + (size_t)(2 * t.g0) * 1024;
+    c.xq = xc + (size_t)(2 * t.g0) * (Ctx::NA * 512);
     c.wq = wc + (size_t)(2 * t.g0) * 1024;
     c.sa_step = (size_t)M * 8;
     c.sb_step = (size_t)N * 8;
     c.sag = xs + t.g0 * c.sa_step;
     c.sbg = ws + t.g0 * c.sb_step;
     c.lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
-    const uint32_t row_group_bytes = (uint32_t)(2 * groups) * 1024u;
+    const uint32_t row_group_bytes = (uint32_t)(2 * groups) * 1024u;   // of the weight; X: NA / 2 times that
     const int rgA = (M + 15) >> 4, rgB = (N + 15) >> 4;
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
         // row groups past the edge are clamped to the last one (their results are never stored)
         const int R = t.m0 + 32 * RT * wave + 32 * i + l32, r = R & 15;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-            c.aoff[i][h] = (uint32_t)min(R >> 4, rgA - 1) * row_group_bytes + r * 64 + (((2 * h + kg) ^ slot_swizzle(r)) << 4);
+        for (int h = 0; h < Ctx::NA; ++h)
+            // 8-bit: K step h / 2 is a piece of its own, and the lane takes half kg of both its blocks
+            c.aoff[i][h] = (uint32_t)min(R >> 4, rgA - 1) * (row_group_bytes * (Ctx::NA / 2)) + (A8 ? (h >> 1) * 1024 : 0) +
+                           r * 64 + (((2 * (A8 ? h & 1 : h) + kg) ^ slot_swizzle(r)) << 4);
         c.sao[i] = (uint32_t)(min(R, M - 1) * 2 + kg) * 4;
     }
     // wave w fetches the 16-column piece w of each of the workgroup's strips
@@ -1230,19 +1243,19 @@ gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const u
     for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = v16f{};
-    batq_u32x4 a[D][RT][2];
+    batq_u32x4 a[D][RT][Ctx::NA];
     int sa[D / 2][RT], sb[D / 2][NJ];
 
     uint4 b[2][NJ][2];
-    mid_prologue<RT, D, NS, 0>(c, a, sa, sb);
+    mid_prologue<RT, D, NS, A8, 0>(c, a, sa, sb);
     // stage 0 has landed: stage indices 1 .. D - 2 may be outstanding
-    wait_vmcnt<(D - 2) / 2 * (MidCtx<RT, D, NS>::count(1) + MidCtx<RT, D, NS>::count(0))>();
+    wait_vmcnt<(D - 2) / 2 * (Ctx::count(1) + Ctx::count(0))>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
-        ready(a[0][i][0]);
-        ready(a[0][i][1]);
+#pragma unroll
+        for (int h = 0; h < Ctx::NA; ++h) ready(a[0][i][h]);
         ready(sa[0][i]);
     }
 #pragma unroll
@@ -1250,9 +1263,9 @@ gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const u
     mid_read_strips<D, NS>(smem, 0, b_rd0, b_rd1, b[0]);
 
     int base = 0;
-    for (; base + 2 * D <= T; base += D) mid_steps<RT, D, NS, 0, true, true>(c, base, smem, b_rd0, b_rd1, acc, a, sa, sb, b);
-    for (; base + D <= T; base += D) mid_steps<RT, D, NS, 0, true>(c, base, smem, b_rd0, b_rd1, acc, a, sa, sb, b);
-    if (base < T) mid_steps<RT, D, NS, 0, false>(c, base, smem, b_rd0, b_rd1, acc, a, sa, sb, b);
+    for (; base + 2 * D <= T; base += D) mid_steps<RT, D, NS, A8, 0, true, true>(c, base, smem, b_rd0, b_rd1, acc, a, sa, sb, b);
+    for (; base + D <= T; base += D) mid_steps<RT, D, NS, A8, 0, true>(c, base, smem, b_rd0, b_rd1, acc, a, sa, sb, b);
+    if (base < T) mid_steps<RT, D, NS, A8, 0, false>(c, base, smem, b_rd0, b_rd1, acc, a, sa, sb, b);
     wait_vmcnt<0>();                                            // the loads past the last stage have landed, too
     // their destinations count as in use until here: a register the compiler took for something else would be
     // overwritten when the load lands
@@ -1260,8 +1273,8 @@ gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const u
     for (int d = 0; d < D; ++d) {
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
-            ready(a[d][i][0]);
-            ready(a[d][i][1]);
+#pragma unroll
+            for (int h = 0; h < Ctx::NA; ++h) ready(a[d][i][h]);
             ready(sa[d >> 1][i]);
         }
 #pragma unroll
@@ -1273,7 +1286,7 @@ gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const u
     if constexpr (std::is_same_v<YT, partial_f32>) {
         store_partial<NJ, RT>(acc, reinterpret_cast<float*>(Y) + t.part * part_stride, lane, wave, 0, t, (int)ldy);
     } else {
-        store_tile<NJ, YT, false, RT>(acc, smem + wave * kEpilogueWaveBytes<RT>, lane, wave, 0, t, M, N, Y, ldy);
+        store_tile<NJ, YT, GLU, RT>(acc, smem + wave * kEpilogueWaveBytes<RT>, lane, wave, 0, t, M, GLU ? N / 2 : N, Y, ldy);
     }
 }
 
@@ -1637,7 +1650,7 @@ struct GemmPlan {
     int ksplit = 1;             // K parts used
     int want = 1;               // K parts the shape would like (workspace permitting)
     int rt = 4;                 // 4-bit tiled kernel: 32-row matrix tiles per wave (4: 4 waves, 2: 8 waves)
-    bool mid = false;           // 4-bit, plain output, at most one gemm_mid workgroup per compute unit
+    bool mid = false;           // at most one gemm_mid workgroup per compute unit
     int mid_strips = 1;         // strips of a gemm_mid workgroup (tile of 128 rows x 64 or 128 columns)
     bool skinny = false, wide = false, narrow = false;
     int cols = 0;               // skinny: workgroups along N
@@ -1674,12 +1687,27 @@ inline GemmPlan gemm_plan(int M, int N, int nb, int cus, bool a8, bool glu, size
         // are too many but pairs of strips fit, a workgroup takes two (tiled kernel -> that: 256 x 4096 x 14336
         // 17.1 -> 16.3 us, 200 rows 15.9 -> 15.4); where single strips fit they are the faster choice (128 x 4096 x
         // 14336: 12.0 us against 16.1 with pairs on half the compute units).
-        if (BATQ_MID && !a8 && !glu && fits32 && g.rt == 4) {
-            const long panels = (M + 127) / 128, strips = g.tiled.strips_n;
+        // The 8-bit and the gated calls follow the same line (8-bit, tiled -> gemm_mid: 100 x 4096 x 4096 18.3 -> 13.2 us,
+        // 333 x 3616 x 5000 20.1 -> 13.2, 512 x 14336 x 4096 50.6 -> 39.4, 1024 x 14336 x 4096 83.3 -> 58.5; gated, two
+        // 4096-wide halves: 100 x 4096 18.3 -> 10.8 with 4-bit, 25.4 -> 15.5 with 8-bit codes).
+        if (BATQ_MID && fits32 && g.rt == 4) {
+            const long panels = (M + 127) / 128, strips = (N + kStrip - 1) / kStrip;
             const bool one = panels * strips * g.ksplit <= g.tiled.workers;
             const bool two = panels * ((strips + 1) / 2) * g.ksplit <= g.tiled.workers;
             g.mid = one || two;
             g.mid_strips = one ? 1 : 2;
+        }
+        // Up to 64 rows the small-M kernel, whose waves share a workgroup's K, has the shorter chain of stages, gemm_mid the
+        // cheaper one (X is read once per 64 columns, with no exchange of partial tiles).  8-bit: gemm_mid once the small-M kernel
+        // needs a second round of workgroups (64 x 4096 x 14336 18.5 -> 14.9 us, 64 x 2048 x 14336 11.0 -> 9.2; with one round
+        // 64 x 4096 x 8192 10.7 -> 13.9).  Gated: the same, and where K has at least 16 groups and a quarter of the compute
+        // units a workgroup (64 x 4096 x 2 x 4096 11.4 -> 10.3 us, 48 x 8192 x 2 x 2048 17.0 -> 15.7, 64 x 4096 x 2 x 14336
+        // 22.9 -> 17.6; but 48 x 2048 x 2 x 4096 5.9 -> 6.4, 64 x 4096 x 2 x 1024 8.4 -> 9.1); 8-bit gated always
+        // (48 x 2048 x 2 x 4096 10.9 -> 8.4 us, 64 x 4096 x 2 x 14336 47.3 -> 21.6).
+        if (M <= 64 && g.mid) {
+            const int cols = (N + (glu ? 63 : 31)) / (glu ? 64 : 32);       // the small-M kernel's workgroups
+            if (glu) g.mid = a8 || cols > cus || (scale_groups(nb) >= 16 && 4 * cols >= cus);
+            else if (a8) g.mid = cols > cus;
         }
         if (M > 64 || g.mid) return g;
         g = GemmPlan();
@@ -1728,24 +1756,23 @@ hipError_t launch_typed(const uint8_t* xc, const uint8_t* xs, const batq_weight*
     if (!g.skinny) {
         const TilePlan& pl = g.tiled;
         if (g.mid) {
-            if constexpr (!A8 && !GLU) {
-                const int ns = g.mid_strips;
-                const dim3 grid((pl.strips_n + ns - 1) / ns, (M + 127) / 128, g.ksplit), block(256);
-                if (g.ksplit > 1) {
-                    partial_f32* const P = reinterpret_cast<partial_f32*>(parts);
-                    if (ns == 2)
-                        gemm_mid<partial_f32, 1, kMidDepth, 2><<<grid, block, 0, stream>>>(
-                            xc, xs, w->d_codes, w->d_scales, M, N, nb, g.ksplit, P, (int64_t)g.col_blocks, (int64_t)g.part_floats);
-                    else
-                        gemm_mid<partial_f32, 1, kMidDepth, 1><<<grid, block, 0, stream>>>(
-                            xc, xs, w->d_codes, w->d_scales, M, N, nb, g.ksplit, P, (int64_t)g.col_blocks, (int64_t)g.part_floats);
-                    splitk_reduce<YT><<<dim3(g.col_blocks, (M + 31) / 32), dim3(256), 0, stream>>>(
-                        parts, g.ksplit, (int64_t)g.part_floats, g.col_blocks, M, N, Y, ldy);
-                } else if (ns == 2) {
-                    gemm_mid<YT, 1, kMidDepth, 2><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, 1, Y, ldy, 0);
-                } else {
-                    gemm_mid<YT, 1, kMidDepth, 1><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, 1, Y, ldy, 0);
-                }
+            const int ns = g.mid_strips;
+            const dim3 grid(((N + kStrip - 1) / kStrip + ns - 1) / ns, (M + 127) / 128, g.ksplit), block(256);
+            auto launch = [&](auto strips, auto* out, int64_t ld, int64_t part_stride) {
+                using T = std::remove_pointer_t<decltype(out)>;
+                gemm_mid<T, 1, kMidDepth, decltype(strips)::value, A8, GLU && !std::is_same_v<T, partial_f32>>
+                    <<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.ksplit, out, ld, part_stride);
+            };
+            auto launch_strips = [&](auto* out, int64_t ld, int64_t part_stride) {
+                if (ns == 2) launch(std::integral_constant<int, 2>{}, out, ld, part_stride);
+                else launch(std::integral_constant<int, 1>{}, out, ld, part_stride);
+            };
+            if (g.ksplit > 1) {
+                launch_strips(reinterpret_cast<partial_f32*>(parts), (int64_t)g.col_blocks, (int64_t)g.part_floats);
+                splitk_reduce<YT><<<dim3(g.col_blocks, (M + 31) / 32), dim3(256), 0, stream>>>(
+                    parts, g.ksplit, (int64_t)g.part_floats, g.col_blocks, M, N, Y, ldy);
+            } else {
+                launch_strips(Y, ldy, 0);
             }
         } else if (g.ksplit > 1) {
             if constexpr (!GLU) {

@@ -137,3 +137,11 @@ def test_linear_glu_is_quantise_then_gemm_glu_and_errors(B):
     assert B.lib.batq_gemm_glu(c.data_ptr(), s.data_ptr(), wgu.handle, M, 4, Hz.data_ptr(), 0, F - 1, None) == 2
     torch.cuda.synchronize()
     assert bool((Hz == 0).all())
+
+
+# the few-row kernel with gated output: 33..64 rows with 16 K groups and 65 strips, pairs of strips (odd number of strips), wave edges
+@pytest.mark.parametrize("M,K,F", [(33, 4096, 2080), (64, 4096 + 32, 224), (40, 64, 8192 + 32), (97, 352, 160), (129, 96, 4128),
+                                   (200, 288, 7200)])
+@pytest.mark.parametrize("bits", [4, 8])
+def test_gemm_glu_few_row_kernel(B, M, K, F, bits):
+    test_gemm_glu_random_codes(B, M, K, F, bits)

@@ -269,3 +269,11 @@ def test_a8w4_linear_configs(B, cfg):
     e4 = np.linalg.norm(got4 - full) / np.linalg.norm(full)
     print(f"cfg {cfg}: rel. error to the unquantised layer: W4A8 {e8:.3f}, W4A4 {e4:.3f}")
     assert e8 < e4
+
+
+# the few-row kernel with 8-bit activations: wave and panel edges, one strip and (odd) pairs of strips per workgroup, a ragged
+# last strip, 2 to 50 stages, K parts; 33 rows by N > 8192 is where it takes over from the small-M kernel
+@pytest.mark.parametrize("M,K,N", [(33, 96, 8200), (64, 288, 14336), (65, 32, 64), (127, 224, 70), (129, 1600, 200),
+                                   (200, 288, 14400 - 7), (1000, 544, 3000), (100, 12288 + 32, 3000)])
+def test_a8w4_few_row_kernel(B, M, K, N):
+    test_a8w4_tile_schedule_shapes(B, M, K, N)
