@@ -1669,6 +1669,7 @@ inline GemmPlan gemm_plan(int M, int N, int nb, int cus, bool a8, bool glu, size
             g.ksplit = g.want > 1 ? choose_ksplit(g.tiled, g.part_floats * sizeof(float), parts_bytes) : 1;
         }
         g.tiled.ksplit = g.ksplit;
+        if (g.ksplit > 1) g.tiled.whole_runs = 0;
         // Eight waves where the workgroups get tiles three or four strips wide: their epilogues and LDS waits then
         // overlap with the other wave's matrix instructions (2048 x 4096 x 14336: 67.8 -> 64.5 us,
         // 8192 x 3584 x 18944: 345 -> 328, 1024 x 4096 x 14336: 38.7 -> 36.3).  Narrow tiles stay with four waves

@@ -19,6 +19,7 @@ struct TilePlan {
     int groups;       // K groups of 256 elements
     int pair;         // 64-column strips per scheduling unit: 1, or 2 when tiles must be an even number of strips
                       // wide (gated output; strips_n then counts units of 128 columns)
+    int whole_runs;   // 1: no share reaches from one run (a row panel of a band) into the next, see worker_share
 };
 
 struct Tile {
@@ -125,33 +126,20 @@ __host__ __device__ inline bool next_tile(const TilePlan& pl, TileWalk& w, Tile&
     return true;
 }
 
-// Column bands: with b bands an XCD's block spans 1/b of N and b/8 of M.  A workgroup walks its strips along N
-// inside a row panel, tile round by tile round (a tile is at most 4 strips wide); the workgroups of an XCD do so in
-// step, so a round streams the block's A rows once more (they do not survive a round in the 4 MiB L2: measured on
-// 8192 x 3584 x 18944 with 4 bands, 10 rounds: 746 MB fetched where one pass over the blocks would be 140 MB)
-// and its share of the B columns once.  The bytes all L2s pull are therefore proportional to
-// rounds * b * M + (8 / b) * N; take the b that minimises it.
-inline int choose_bands(int M, int N, int strips_n, int tiles_m, int workers) {
-    const long strips = (long)tiles_m * strips_n;
-    const long per_worker = (strips + workers - 1) / workers;
-    const long rounds = per_worker > 4 ? (per_worker + 3) / 4 : 1;
-    int best = 1;
-    double best_cost = 1e300;
-    for (int b = 1; b <= 8; b *= 2) {
-        if (b > strips_n) break;
-        const double cost = (double)rounds * b * M + (8.0 / b) * N;
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = b;
-        }
-    }
-    return best;
+// First of the shares that start at or after unit `pos` when the shares are dealt out run by run: the workgroups in proportion
+// to the units in front of `pos`, rounded (total < 2^20, workers <= 2^11).
+__host__ __device__ inline int shares_before(const TilePlan& pl, int pos, int total) {
+    return (int)(((uint32_t)pos * (uint32_t)pl.workers + (uint32_t)total / 2) / (uint32_t)total);
 }
-
 
 // The share of the linear order that workgroup `block` of `pl.workers` works on: workgroups go to the 8 XCDs
 // round-robin, so workgroup b takes share (b % 8) * (workers / 8) + b / 8 and the shares of one XCD are
 // contiguous.
+// A tile cannot reach into the next run (row panel of a band), so a share that does costs an extra, narrower tile, and its
+// workgroup is the one the launch waits for (two tiles of one strip take nearly twice as long as one of two).  Where the
+// shares come in two sizes anyway, whole_runs deals the workgroups out run by run and lets each run's workgroups
+// share it evenly: the same two sizes, and no share in two runs (graph-replayed, 700 x 4096 x 8192: 25.5 -> 22.4 us,
+// with 8-bit codes 42.1 -> 30.3; 2500 x 4096 x 4096 32.4 -> 27.8, 49.6 -> 38.3; 2300 x 4096 x 14336 73.0 -> 68.5, 107.7 -> 94.2).
 __host__ __device__ inline void worker_share(const TilePlan& pl, int block, int& cur, int& end) {
     const int per_xcd = pl.workers >> 3;
     const int share = (block & 7) * per_xcd + (block >> 3);
@@ -159,12 +147,109 @@ __host__ __device__ inline void worker_share(const TilePlan& pl, int block, int&
     if (total < (1 << 20)) {                    // the usual case: 32-bit products and divisions (workers <= 2^11)
         const uint32_t t32 = (uint32_t)total, wk = (uint32_t)pl.workers;
         cur = (int)(t32 * (uint32_t)share / wk);
+        if (pl.whole_runs) {
+            // the run of an even share is this one's or a neighbour of it
+            int b = 0;
+            while (b + 1 < pl.bands && cur >= pl.tiles_m * ((b + 1) * pl.strips_n / pl.bands)) ++b;
+            int bs = b * pl.strips_n / pl.bands, width = (b + 1) * pl.strips_n / pl.bands - bs;
+            int start = pl.tiles_m * bs + (cur - pl.tiles_m * bs) / width * width;
+            int first = shares_before(pl, start, (int)t32), last = shares_before(pl, start + width, (int)t32);
+            while (share < first || share >= last) {
+                if (share < first) {
+                    if (start == pl.tiles_m * bs) {                 // into the band before
+                        --b;
+                        bs = b * pl.strips_n / pl.bands;
+                        width = (b + 1) * pl.strips_n / pl.bands - bs;
+                    }
+                    start -= width;
+                } else {
+                    start += width;
+                    if (start == pl.tiles_m * (bs + width)) {       // into the next band
+                        ++b;
+                        bs = b * pl.strips_n / pl.bands;
+                        width = (b + 1) * pl.strips_n / pl.bands - bs;
+                    }
+                }
+                first = shares_before(pl, start, (int)t32);
+                last = shares_before(pl, start + width, (int)t32);
+            }
+            const uint32_t n = (uint32_t)(last - first), i = (uint32_t)(share - first);
+            cur = start + (int)((uint32_t)width * i / n);
+            end = start + (int)((uint32_t)width * (i + 1) / n);
+            return;
+        }
         end = (int)(t32 * (uint32_t)(share + 1) / wk);
         return;
     }
     cur = (int)(total * share / pl.workers);
     end = (int)(total * (share + 1) / pl.workers);
 }
+
+// What the ends of the runs mean for a plan's shares: 0 - no share in two runs takes more tiles for it than the largest share does
+// alone; 1 - some do, and whole_runs avoids it: the shares come in two sizes, and every run can be made up of the
+// workgroups that fall to it with those; 2 - some do, and it cannot.  (More than 64 runs, i.e. 2: not looked into,
+// for the host's time.)
+inline int run_ends(const TilePlan& pl) {
+    const int64_t total = (int64_t)pl.tiles_m * pl.strips_n, runs = (int64_t)pl.tiles_m * pl.bands;
+    if (pl.workers > 2048 || total >= (1 << 20) || total <= pl.workers) return 0;
+    if (runs > 64) return 2;
+    const int lo = (int)(total / pl.workers), hi = (int)((total + pl.workers - 1) / pl.workers);
+    bool costly = false, possible = hi > lo;
+    int pos = 0, first = 0;
+    for (int b = 0; b < pl.bands; ++b) {
+        const int width = (b + 1) * pl.strips_n / pl.bands - b * pl.strips_n / pl.bands;
+        for (int p = 0; p < pl.tiles_m; ++p) {
+            pos += width;
+            const int last = shares_before(pl, pos, (int)total), n = last - first;
+            if (n * lo > width || n * hi < width) possible = false;
+            first = last;
+            // the even share that holds unit pos
+            const int64_t s = (((int64_t)pos + 1) * pl.workers - 1) / total;
+            const int cur = (int)(total * s / pl.workers), end = (int)(total * (s + 1) / pl.workers);
+            if (cur < pos && pos < end && run_tiles(pl, pos - cur) + run_tiles(pl, end - pos) > run_tiles(pl, hi)) costly = true;
+        }
+    }
+    return !costly ? 0 : possible ? 1 : 2;
+}
+
+// Column bands: with b bands an XCD's block spans 1/b of N and b/8 of M.  A workgroup walks its strips along N
+// inside a row panel, tile round by tile round (a tile is at most 4 strips wide); the workgroups of an XCD do so in
+// step, so a round streams the block's A rows once more (they do not survive a round in the 4 MiB L2: measured on
+// 8192 x 3584 x 18944 with 4 bands, 10 rounds: 746 MB fetched where one pass over the blocks would be 140 MB)
+// and its share of the B columns once.  The bytes all L2s pull are therefore proportional to
+// rounds * b * M + (8 / b) * N; take the b that minimises it.
+// Where that b leaves shares in two runs (run_ends 2) and another does not, the next cheapest of those serves as long as its
+// bytes stay below 1.4 times the least; with one tile per workgroup any b will do.  (5293 x 4096 x 6075 at 1.30 times the bytes
+// 73.2 -> 70.5 us with 4-bit, 111.7 -> 104.6 with 8-bit codes; 3669 x 4096 x 9865 at 1.46 times 90.4 -> 92.2, 135.1 -> 128.2;
+// one tile each, 2720 x 4096 x 5802: 41.3 -> 38.7, 64.3 -> 55.8.)
+inline void choose_bands(TilePlan& pl, int M, int N) {
+    const long strips = (long)pl.tiles_m * pl.strips_n;
+    const long per_worker = (strips + pl.workers - 1) / pl.workers;
+    const long rounds = per_worker > 4 ? (per_worker + 3) / 4 : 1;
+    double cost[4], limit = 1e300;
+    for (int i = 0; i < 4; ++i) cost[i] = (1 << i) <= pl.strips_n ? (double)(rounds << i) * M + (8.0 / (1 << i)) * N : 1e300;
+    for (int tries = 0, first = 0; tries < 4; ++tries) {
+        int best = 0;
+        for (int i = 1; i < 4; ++i)
+            if (cost[i] < cost[best]) best = i;
+        if (cost[best] >= limit) {                     // no better one: the cheapest after all
+            pl.bands = 1 << first;
+            pl.whole_runs = 0;
+            return;
+        }
+        pl.bands = 1 << best;
+        const int ends = run_ends(pl);
+        pl.whole_runs = ends == 1;
+        if (ends != 2) return;
+        if (tries == 0) {
+            first = best;
+            limit = rounds == 1 ? 1e299 : 1.4 * cost[best];
+        }
+        cost[best] = 1e300;
+    }
+    pl.whole_runs = 0;
+}
+
 
 // K parts wanted for a plan without them: fewer strips than half the workgroups (few rows, narrow N) and a
 // long K.  A part keeps at least 12 K groups: below that the partial sums' round trip costs more than the
@@ -185,9 +270,11 @@ inline TilePlan make_plan(int M, int N, int nb, int cus, bool glu) {
     pl.tiles_m = (M + kTile - 1) / kTile;
     pl.strips_n = (N + kStrip * pl.pair - 1) / (kStrip * pl.pair);
     pl.workers = 8 * (cus / 8 > 1 ? cus / 8 : 1);       // one persistent workgroup per compute unit
-    pl.bands = choose_bands(M, N, pl.strips_n, pl.tiles_m, pl.workers);
+    pl.bands = 1;
     pl.ksplit = 1;
     pl.groups = (nb + 7) / 8;
+    pl.whole_runs = 0;
+    choose_bands(pl, M, N);
     return pl;
 }
 

@@ -133,3 +133,16 @@ def test_invalid_arguments(lib):
     assert lib.batq_debug_tile_schedule(100, 128, 100, 256, 0, 0, None, 0) == -1
     assert lib.batq_debug_tile_schedule(100, 96, 256, 256, 1, 0, None, 0) == -1     # gated output needs N % 64 == 0
     assert lib.batq_debug_tile_schedule(100, 128, 256, 256, 0, 0, None, 5) == -1
+
+
+@pytest.mark.parametrize("M,N,glu", [(700, 8192, False), (3449, 2963, False), (5327, 1786, False), (2300, 14336, False),
+                                     (2720, 5802, False), (1290, 17749, False), (5293, 6075, False), (2500, 4096, False),
+                                     (700, 16384, True), (2500, 8192, True)])
+def test_no_share_reaches_into_the_next_run(lib, M, N, glu):
+    """A share that crosses from one row panel of a band into the next takes an extra tile, and the launch waits for it:
+    where the shares come in two sizes every workgroup gets as few tiles as the larger size needs."""
+    t = _check(lib, M, N, 4096, 256, glu, False)
+    units = (-(-M // 256)) * (-(-N // (128 if glu else 64)))
+    assert units % 256 and units > 256
+    most = -(-(units // 256 + 1) // (2 if glu else 4))
+    assert np.bincount(t[:, 0]).max() == most
