@@ -8,7 +8,7 @@
 // (8*(r/4) + 4*(l/32) + r%4, l % 32) of the 32x32 tile.
 //
 // Kernels:
-//   gemm_skinny - M <= 64: 32 output columns per workgroup, K split over its 8 waves.
+//   gemm_skinny - M <= 64: 16 to 64 output columns per workgroup, K split over its 8 waves.
 //   gemm_tiled  - persistent workgroups of 4 or 8 waves, output tiles of 256 rows x 64..256 columns;
 //                 codes and scales stream global -> LDS with LDS-direct loads through a 4-stage ring
 //                 (XOR-swizzled 16-byte slots); every workgroup takes an equal share of the output,
@@ -203,7 +203,7 @@ gemm_direct(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, cons
 
 // ------------------------------------------------------------------------------------------
 // Small M (decode shapes): the time goes into streaming the weight codes once, so the work is
-// split along K as well.  A workgroup of 8 waves owns 32 output columns (all rows); wave w takes an
+// split along K as well.  A workgroup of 8 waves owns up to 32 or 64 output columns (all rows); wave w takes an
 // equal share of the K groups (256 elements = 4 matrix instructions, whose 8 scale bytes per row
 // are two dwords), issues all loads of a group before its matrix instructions, and the 8 partial
 // tiles are summed through LDS in a fixed order.  K is zero-padded to whole groups in both
@@ -211,24 +211,22 @@ gemm_direct(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, cons
 constexpr int kSkinnyWaves = 8;
 
 // RT = 32-row tiles of X handled together (1 or 2), sharing the weight loads; A8 = MXFP8 activations;
-// GLU = gated output: a workgroup owns 32 output columns = the 32 gate and the 32 up columns of one
-// 64-column group of the interleaved weight (sharing the loads of X), and stores silu(gate) * up to M x N/2.
-// WIDE (not with GLU): a workgroup owns 64 output columns instead of 32, which halves how often the X codes
-// are read; used when N is large enough that 64-column workgroups still fill the chip.
-// NARROW (not with GLU or WIDE): a workgroup owns 16 output columns, for N so small that 32-column workgroups would
-// leave half the compute units without one: lanes 16-31 of each half wave load what lanes 0-15 load (the same cache
-// lines) and their columns of the matrix instructions' results are dropped.
-template <typename YT, int RT, bool A8, bool GLU, bool WIDE, bool NARROW = false>
+// GLU = gated output: the gate and the up columns of a workgroup's outputs in the interleaved weight are two matrix tiles
+// (sharing the loads of X), and silu(gate) * up goes to M x N/2.
+// WIDE (not with GLU): two matrix tiles of columns, which halves how often the X codes are read.
+// A workgroup owns `unit` output columns, at most 32 (WIDE: 64), so that the columns can be split evenly over the compute
+// units (gemm_plan); lanes beyond them load what the last one loads (the same cache lines) and their columns of the matrix
+// instructions' results are dropped.
+template <typename YT, int RT, bool A8, bool GLU, bool WIDE>
 __global__ void __launch_bounds__(kSkinnyWaves * 64)
 gemm_skinny(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const uint8_t* __restrict__ wc,
-            const uint8_t* __restrict__ ws, int M, int N, int nb, YT* __restrict__ Y, int64_t ldy,
+            const uint8_t* __restrict__ ws, int M, int N, int nb, int unit, YT* __restrict__ Y, int64_t ldy,
             float* __restrict__ partial) {
     static_assert(!(GLU && WIDE), "the gated kernel already takes two column groups");
-    static_assert(!(NARROW && (GLU || WIDE)), "16 columns only for the plain kernel");
     constexpr int NG = (GLU || WIDE) ? 2 : 1;               // 32-column groups of the weight per workgroup
     __shared__ float part[kSkinnyWaves][16][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n0 = blockIdx.x * (NARROW ? 16 : 32 * NG);    // first weight column
+    const int n0 = blockIdx.x * unit;                       // first output column
     const int i = lane & 31, kg = lane >> 5;
     const int groups = scale_groups(nb);
     // gridDim.y > 1: the K groups are first cut into gridDim.y parts, one per workgroup row, whose sums go
@@ -240,7 +238,14 @@ gemm_skinny(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, cons
     const uint8_t* pb[NG];
 #pragma unroll
     for (int c = 0; c < NG; ++c) {
-        bn[c] = min(n0 + 32 * c + (NARROW ? (i & 15) : i), N - 1);   // rows and columns past the edge are computed, not stored
+        // columns past the unit or the edge are computed (from a column that is loaded anyway) and not stored, like rows
+        // past the edge
+        if constexpr (GLU) {
+            const int o = min(n0 + min(i, unit - 1), N / 2 - 1);
+            bn[c] = 64 * (o >> 5) + 32 * c + (o & 31);
+        } else {
+            bn[c] = min(n0 + min(32 * c + i, unit - 1), N - 1);
+        }
         const int rb = bn[c] & 15;
         pb[c] = wc + (size_t)(bn[c] >> 4) * code_stages(nb) * 1024 + rb * 64;
         swb[c] = (rb >> 2) & 3;
@@ -347,13 +352,13 @@ gemm_skinny(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, cons
             const int r = e >> 6, l = e & 63;
             const int row = 32 * t + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
             if constexpr (GLU) {
-                const int col = blockIdx.x * 32 + (l & 31);
-                if (row < M && col < N / 2) store_y<YT>(Y + (size_t)row * ldy + col, swiglu_f32(v[0][h], v[1][h]));
+                const int col = n0 + (l & 31);
+                if (row < M && (l & 31) < unit && col < N / 2) store_y<YT>(Y + (size_t)row * ldy + col, swiglu_f32(v[0][h], v[1][h]));
             } else {
 #pragma unroll
                 for (int c = 0; c < NG; ++c) {
                     const int col = n0 + 32 * c + (l & 31);
-                    if (row < M && col < N && (!NARROW || (l & 31) < 16)) {
+                    if (row < M && 32 * c + (l & 31) < unit && col < N) {
                         if (gridDim.y > 1) partial[((size_t)blockIdx.y * M + row) * N + col] = v[c][h];
                         else store_y<YT>(Y + (size_t)row * ldy + col, v[c][h]);
                     }
@@ -1652,8 +1657,8 @@ struct GemmPlan {
     int rt = 4;                 // 4-bit tiled kernel: 32-row matrix tiles per wave (4: 4 waves, 2: 8 waves)
     bool mid = false;           // at most one gemm_mid workgroup per compute unit
     int mid_strips = 1;         // strips of a gemm_mid workgroup (tile of 128 rows x 64 or 128 columns)
-    bool skinny = false, wide = false, narrow = false;
-    int cols = 0;               // skinny: workgroups along N
+    bool skinny = false, wide = false;
+    int cols = 0, unit = 0;     // skinny: workgroups along N and output columns of each
 };
 
 // fits32: both code arrays are below 2 GiB (the tiled kernels and gemm_mid use 32-bit load offsets; M > 64 without
@@ -1716,17 +1721,38 @@ inline GemmPlan gemm_plan(int M, int N, int nb, int cus, bool a8, bool glu, size
     g.skinny = true;
     // 64 columns per workgroup pay with two row tiles (the X codes are the larger share of a workgroup's
     // loads then) when they make one full round of workgroups: between three quarters of and all the compute
-    // units (64 x 4096 x 14336: 15.4 -> 12.9 us; with one row tile, or a second partial round, it loses).  Not
-    // for the 8-bit kernel, which would not fit its registers.
+    // units (64 x 4096 x 14336: 15.4 -> 12.9 us; with a second partial round it loses).  Not for the 8-bit
+    // kernel, which would not fit its registers.
     const int cols64 = (N + 63) / 64;
     g.wide = !glu && !a8 && M > 32 && cols64 <= cus && 4 * cols64 >= 3 * cus;
-    // 16 columns per workgroup where 32 would give at most half the compute units a workgroup (decode shapes with
-    // N <= 4096 on 256 compute units; graph-replayed, 20 weight copies taking turns: 16 x 4096 x 4096 4.7 -> 4.5 us,
-    // 16 x 14336 x 4096 11.2 -> 10.2 us, where it also replaces two K parts and their second kernel,
-    // 32 x 8192 x 2048 7.0 -> 6.8).  (Four instead of two K groups in flight per wave, with a ring of register sets:
-    // 16 x 14336 x 4096 back to 11.2 us; not in.)
-    g.narrow = !glu && !g.wide && M <= 32 && 2 * ((N + 31) / 32) <= cus;
-    g.cols = (glu || g.wide) ? cols64 : g.narrow ? (N + 15) / 16 : (N + 31) / 32;
+    // Up to 32 rows the time is the weight stream, so every compute unit should pull the same share of it: the columns are
+    // cut into equal units of 16 to 32 (plain, wide: to 64) for one or a few rounds of workgroups, instead of fixed ones that
+    // leave compute units without a workgroup or give some twice the columns of others (graph-replayed, weight copies taking
+    // turns, units of 32 -> equal ones: 16 x 4096 x 11008 9.2 -> 8.6 us, 16 x 8192 x 8960 13.7 -> 12.4, 16 x 4096 x 6144 5.6 -> 5.3,
+    // gated 16 x 4096 x 2 x 12032 16.3 -> 15.1, 1 x 4096 x 2 x 14336 15.8 -> 15.5; 16 instead of 32 columns for N <= 4096:
+    // 16 x 14336 x 4096 11.2 -> 10.2).  One wide unit instead of two of up to 32 shares the X loads and has one reduction:
+    // 8-bit 16 x 4096 x 14336 11.5 -> 10.3 us, 16 x 8192 x 8960 15.9 -> 13.2, 32 x 4096 x 10240 11.8 -> 9.5; 4-bit up to 48 columns
+    // (16 x 8192 x 8960 12.4 -> 11.7, 32 x 4096 x 10240 9.6 -> 8.8) and beyond that with more than 16 rows (x 4096 x 14336:
+    // 32 rows 10.9 -> 10.3, one row 8.1 -> 8.8), but not in a second round (16 x 4096 x 18944 11.1 -> 12.9) nor
+    // where K has fewer groups than a workgroup has waves (32 x 1024 x 16384 4.3 -> 4.7).
+    const int n_out = glu ? N / 2 : N;                      // a gated unit: 32 outputs = 64 weight columns
+    g.unit = g.wide ? 64 : 32;
+    if (M <= 32) {
+        auto even_unit = [&](int most) {
+            const int rounds = (n_out + most * cus - 1) / (most * cus);
+            // K with fewer groups than a workgroup has waves: launch-bound, more workgroups only read X more often
+            // (gated 30 x 1024 x 2 x 6400 4.18 us with units of 32, 4.30 with 28)
+            if (rounds == 1 && n_out > 16 * cus && scale_groups(nb) < kSkinnyWaves) return most;
+            return std::max(16, ((n_out + rounds * cus - 1) / (rounds * cus) + 3) & ~3);
+        };
+        g.unit = even_unit(32);
+        if (!glu && n_out > 32 * cus) {
+            const int both = even_unit(64);
+            g.wide = a8 || (n_out <= 64 * cus && scale_groups(nb) >= kSkinnyWaves && (both <= 48 || M > 16));
+            if (g.wide) g.unit = both;
+        }
+    }
+    g.cols = (n_out + g.unit - 1) / g.unit;
     // Narrow N with a long K leaves half the compute units idle while every workgroup reads all of A: two
     // workgroup rows then take half of K each (64 x 14336 x 4096: 15.8 -> 12.0 us).  More parts, or shorter
     // K, lose more to the second kernel than they gain.
@@ -1814,19 +1840,19 @@ hipError_t launch_typed(const uint8_t* xc, const uint8_t* xs, const batq_weight*
         float* pp = g.ksplit > 1 ? parts : nullptr;
         if constexpr (GLU) {
             if (M <= 32)
-                gemm_skinny<YT, 1, A8, true, false><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, Y, ldy, pp);
+                gemm_skinny<YT, 1, A8, true, false><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.unit, Y, ldy, pp);
             else
-                gemm_skinny<YT, 2, A8, true, false><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, Y, ldy, pp);
+                gemm_skinny<YT, 2, A8, true, false><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.unit, Y, ldy, pp);
         } else if (g.wide) {
-            if constexpr (!A8)
-                gemm_skinny<YT, 2, false, false, true><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, Y, ldy, pp);
-        } else if (g.narrow) {
-            gemm_skinny<YT, 1, A8, false, false, true><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, Y, ldy, pp);
+            if (M <= 32)
+                gemm_skinny<YT, 1, A8, false, true><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.unit, Y, ldy, pp);
+            else if constexpr (!A8)
+                gemm_skinny<YT, 2, false, false, true><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.unit, Y, ldy, pp);
         } else {
             if (M <= 32)
-                gemm_skinny<YT, 1, A8, false, false><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, Y, ldy, pp);
+                gemm_skinny<YT, 1, A8, false, false><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.unit, Y, ldy, pp);
             else
-                gemm_skinny<YT, 2, A8, false, false><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, Y, ldy, pp);
+                gemm_skinny<YT, 2, A8, false, false><<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.unit, Y, ldy, pp);
         }
         if (g.ksplit > 1) {
             const int64_t total = (int64_t)M * N;

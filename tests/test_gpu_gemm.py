@@ -358,3 +358,11 @@ def test_weight_codes_of_two_gib(B):
         tol = 1e-6 * (np.abs(o.dequantize(xc, xs)) @ np.abs(o.dequantize(wc, ws)).T)
         assert np.all(np.abs(got - ref) <= tol + 1e-30), M
         assert bool(torch.isfinite(Y).all())
+
+
+@pytest.mark.parametrize("M,K,N", [(3, 2080, 5000), (1, 2080, 8196), (16, 288, 14336), (17, 2080, 14336), (32, 64, 18944 + 5),
+                                   (8, 2304, 8200)])
+def test_small_m_even_units(B, M, K, N):
+    """Up to 32 rows the columns are cut into equal units for the compute units: 20 columns, 36 and 56 as two matrix
+    tiles, 28, and a third round of workgroups; ragged last units."""
+    test_small_shapes_random_codes(B, M, K, N)

@@ -277,3 +277,9 @@ def test_a8w4_linear_configs(B, cfg):
                                    (200, 288, 14400 - 7), (1000, 544, 3000), (100, 12288 + 32, 3000)])
 def test_a8w4_few_row_kernel(B, M, K, N):
     test_a8w4_tile_schedule_shapes(B, M, K, N)
+
+
+# units of 20 columns, of 36, 56 and (second round) 40 as two matrix tiles, ragged last units
+@pytest.mark.parametrize("M,K,N", [(3, 2080, 5000), (1, 2080, 8196), (32, 2080, 14336), (16, 64, 18944 + 5)])
+def test_a8w4_small_m_even_units(B, M, K, N):
+    test_a8w4_tile_schedule_shapes(B, M, K, N)
