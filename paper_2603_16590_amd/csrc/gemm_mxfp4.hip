@@ -1181,13 +1181,21 @@ __device__ __forceinline__ void mid_steps(MidCtx<RT, D, NS, A8>& c, int base, co
     }
 }
 
-// Requires operand code arrays below 2 GiB (32-bit load offsets).  Grid: (groups of NS strips, row panels of 128 RT,
-// K parts); YT = partial_f32: partial sums of K part blockIdx.z in store_partial order (ldy = 32-column blocks of the
+// Which tile a workgroup takes.  Workgroups go to the 8 XCDs round-robin, so in the plain order (groups of NS strips, row
+// panels of 128 RT, K parts) the panels of one strip land on different XCDs unless the number of groups is a multiple of 8, and
+// every one of their L2s pulls the strip's weights.  In the other two orders gridDim.x is 8, so that blockIdx.x is the XCD:
+// kMidByStrip gives an XCD every eighth group of strips with all panels, kMidByPanel every eighth panel with all strips.
+// Quantiser and GEMM, graph-replayed, weights in HBM: 3000 x 2048 x 600 17.3 -> 14.3 us (8-bit 21.7 -> 17.7), 2000 x 512 x 700
+// 8.9 -> 8.1 (10.6 -> 9.3), 200 x 4096 x 9000 19.1 -> 18.0, 333 x 3616 x 5000 14.0 -> 13.6, gated 1000 x 2048 x 2 x 1568
+// 15.8 -> 14.1 (18.9 -> 16.9).
+enum MidOrder { kMidPlain = 0, kMidByStrip = 1, kMidByPanel = 2 };
+
+// Requires operand code arrays below 2 GiB (32-bit load offsets).  Grid: see MidOrder; YT = partial_f32: partial sums of K part blockIdx.z in store_partial order (ldy = 32-column blocks of the
 // padded output, part_stride = floats of a part).
 template <typename YT, int RT, int D, int NS, bool A8, bool GLU>
 __global__ void __launch_bounds__(256, A8 && NS == 2 ? 1 : 2)
 gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const uint8_t* __restrict__ wc,
-         const uint8_t* __restrict__ ws, int M, int N, int nb, int ksplit, YT* __restrict__ Y, int64_t ldy,
+         const uint8_t* __restrict__ ws, int M, int N, int nb, int ksplit, int order, YT* __restrict__ Y, int64_t ldy,
          int64_t part_stride) {
     constexpr int NJ = 2 * NS;
     __shared__ __align__(16) uint8_t smem[D * NS * kMidStripLds];
@@ -1196,10 +1204,23 @@ gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const u
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int groups = (nb + 7) >> 3;
     Tile t;
-    t.n0 = blockIdx.x * (kStrip * NS);
-    t.m0 = blockIdx.y * (128 * RT);
-    t.nj = NS;
+    int strip = blockIdx.x, panel = blockIdx.y;
     t.part = blockIdx.z;
+    if (order != kMidPlain) {
+        int eight = blockIdx.z;                                 // which of the XCD's strips (panels)
+        t.part = 0;
+        if (ksplit > 1) {
+            const int per_part = (int)gridDim.z / ksplit;
+            t.part = eight / per_part;
+            eight -= t.part * per_part;
+        }
+        strip = order == kMidByStrip ? blockIdx.x + 8 * eight : blockIdx.y;
+        panel = order == kMidByStrip ? blockIdx.y : blockIdx.x + 8 * eight;
+    }
+    t.n0 = strip * (kStrip * NS);
+    t.m0 = panel * (128 * RT);
+    t.nj = NS;
+    if (t.n0 >= N || t.m0 >= M) return;                         // workgroup-uniform (the last of eight)
     t.g0 = 0;
     t.ng = groups;
     if (ksplit > 1) {                                           // (divisions only where there are K parts)
@@ -1784,11 +1805,30 @@ hipError_t launch_typed(const uint8_t* xc, const uint8_t* xs, const batq_weight*
         const TilePlan& pl = g.tiled;
         if (g.mid) {
             const int ns = g.mid_strips;
-            const dim3 grid(((N + kStrip - 1) / kStrip + ns - 1) / ns, (M + 127) / 128, g.ksplit), block(256);
+            const int gx = ((N + kStrip - 1) / kStrip + ns - 1) / ns, gy = (M + 127) / 128;
+            int order = kMidPlain;
+            if (gy > 1 && gx % 8 != 0) {                    // (a multiple of 8 groups: the plain order is kMidByStrip's)
+                // Only where the XCDs' shares are alike (at most an eighth of the last round is missing), no XCD gets more
+                // workgroups than compute units, and what every XCD pulls (X or the weight) leaves room in its 4 MiB L2 (900 x
+                // 4096 x 1984 with 8-bit X, 3.7 MB: 20.3 -> 21.2 us); of the two the one that pulls fewer bytes.
+                const int parts_k = g.ksplit;
+                auto fits = [&](int n, int other, size_t common) {
+                    const int per_xcd = (n + 7) / 8;
+                    return (8 * per_xcd - n) * 8 <= n && (long)per_xcd * other * parts_k <= cus / 8 && common <= (3u << 20);
+                };
+                const size_t x_bytes = (size_t)M * nb * (A8 ? 32 : 16), w_bytes = (size_t)N * nb * 16;
+                const bool strips = fits(gx, gy, x_bytes), panels = fits(gy, gx, w_bytes);
+                if (panels && (!strips || x_bytes / 8 + w_bytes < x_bytes + w_bytes / 8)) order = kMidByPanel;
+                else if (strips) order = kMidByStrip;
+            }
+            const dim3 grid = order == kMidPlain ? dim3(gx, gy, g.ksplit)
+                              : order == kMidByStrip ? dim3(8, gy, (gx + 7) / 8 * g.ksplit)
+                                                     : dim3(8, gx, (gy + 7) / 8 * g.ksplit);
+            const dim3 block(256);
             auto launch = [&](auto strips, auto* out, int64_t ld, int64_t part_stride) {
                 using T = std::remove_pointer_t<decltype(out)>;
                 gemm_mid<T, 1, kMidDepth, decltype(strips)::value, A8, GLU && !std::is_same_v<T, partial_f32>>
-                    <<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.ksplit, out, ld, part_stride);
+                    <<<grid, block, 0, stream>>>(xc, xs, w->d_codes, w->d_scales, M, N, nb, g.ksplit, order, out, ld, part_stride);
             };
             auto launch_strips = [&](auto* out, int64_t ld, int64_t part_stride) {
                 if (ns == 2) launch(std::integral_constant<int, 2>{}, out, ld, part_stride);

@@ -366,3 +366,12 @@ def test_small_m_even_units(B, M, K, N):
     """Up to 32 rows the columns are cut into equal units for the compute units: 20 columns, 36 and 56 as two matrix
     tiles, 28, and a third round of workgroups; ragged last units."""
     test_small_shapes_random_codes(B, M, K, N)
+
+
+@pytest.mark.parametrize("M,K,N", [(333, 96, 5000), (2000, 64, 700), (129, 64, 4040), (300, 6144, 1984 - 5), (1030, 96, 640 - 3)])
+def test_few_row_kernel_tile_orders(B, M, K, N):
+    """Several row panels and a number of strips that is no multiple of 8: an XCD takes every eighth strip or every
+    eighth panel, with and without K parts, one missing of the last eight.  (Element by element: with only 64 to 96
+    products a sum of random codes is often a bf16 tie, which a last-bit difference of the fp32 sum turns by one bf16
+    unit, up to 2^-8; a tie in 12 sums is already 2^-8 / sqrt(12) = 1.1e-3 in the Frobenius norm of all of them.)"""
+    test_split_k_shapes(B, M, K, N) if K >= 6144 else _check_every_element(B, M, K, N)
