@@ -27,7 +27,7 @@ struct batq_transform {
     float* d_clip = nullptr;      // [nb], 1.0 when no clipping
     float* d_clip_max = nullptr;  // [nb], only when minmax
     double* d_Tinv = nullptr;     // [nb][32][32] fp64 T_k^-1     (null when !has_transform)
-    double* d_outer_inv = nullptr;   // Kronecker forms: fp64 inverses of the factors, laid out as d_outer / d_inner
+    double* d_outer_inv = nullptr;   // Kronecker forms: fp64 inverses of the factors, laid out as d_outer / d_inner, in d_Tinv's allocation
     double* d_inner_inv = nullptr;
     double* d_Tf64 = nullptr;     // [nb][32][32] fp64 T_k        (null when !has_transform)
     uint16_t* d_Tsplit = nullptr; // [nb][3][2][64][8] bf16 three-term split of T_k in MFMA operand order
