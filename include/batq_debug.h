@@ -17,9 +17,10 @@ extern "C" {
  * with at most one 128 x 64 tile per compute unit go to another kernel, one tile per workgroup).  Writes 7 ints per
  * tile to tiles[capacity * 7] (HOST): workgroup, first row, first column, width in 64-column strips, K part,
  * first K group (256 elements) and number of K groups; returns the number of tiles (also when capacity is
- * smaller; -1 for invalid arguments).  glu: the gated-output mode of batq_gemm_glu (N % 64 == 0);
+ * smaller; -1 for invalid arguments).  mode: bit 0 the gated output of batq_gemm_glu (N % 64 == 0), bit 1 8-bit
+ * activation codes;
  * allow_ksplit: K parts as chosen with a workspace of batq_gemm_workspace() bytes.  For tests of the schedule. */
-int batq_debug_tile_schedule(int M, int N, int K, int compute_units, int glu, int allow_ksplit,
+int batq_debug_tile_schedule(int M, int N, int K, int compute_units, int mode, int allow_ksplit,
                              int* tiles, int capacity);
 
 #ifdef __cplusplus

@@ -1687,7 +1687,7 @@ struct GemmPlan {
 inline GemmPlan gemm_plan(int M, int N, int nb, int cus, bool a8, bool glu, size_t parts_bytes, bool fits32 = true) {
     GemmPlan g;
     if (M > 32) {
-        g.tiled = make_plan(M, N, nb, cus, glu);
+        g.tiled = make_plan(M, N, nb, cus, glu, a8);
         if (!glu) {
             g.col_blocks = 2 * g.tiled.strips_n;
             g.part_floats = (size_t)g.tiled.tiles_m * 8 * g.col_blocks * kPartialBlockFloats;
@@ -1954,10 +1954,10 @@ hipError_t launch_codes8_to_rowmajor(const uint8_t* blocked, uint8_t* rowmajor, 
     return hipGetLastError();
 }
 
-int tile_schedule(int M, int N, int K, int compute_units, bool glu, bool allow_ksplit, int* out, int capacity) {
+int tile_schedule(int M, int N, int K, int compute_units, bool glu, bool a8, bool allow_ksplit, int* out, int capacity) {
     const int nb = K / 32;
     if (M <= 64) return 0;                                      // the small-M kernels have no tile schedule
-    const GemmPlan g = gemm_plan(M, N, nb, compute_units, false, glu, allow_ksplit ? ~size_t(0) : 0);
+    const GemmPlan g = gemm_plan(M, N, nb, compute_units, a8, glu, allow_ksplit ? ~size_t(0) : 0);
     const TilePlan& pl = g.tiled;
     int n = 0;
     for (int b = 0; b < pl.workers; ++b) {

@@ -222,21 +222,24 @@ inline int run_ends(const TilePlan& pl) {
 // bytes stay below 1.4 times the least; with one tile per workgroup any b will do.  (5293 x 4096 x 6075 at 1.30 times the bytes
 // 73.2 -> 70.5 us with 4-bit, 111.7 -> 104.6 with 8-bit codes; 3669 x 4096 x 9865 at 1.46 times 90.4 -> 92.2, 135.1 -> 128.2;
 // one tile each, 2720 x 4096 x 5802: 41.3 -> 38.7, 64.3 -> 55.8.)
-inline void choose_bands(TilePlan& pl, int M, int N) {
+// Where every b leaves such shares, the cheapest serves after all: more bands are more runs, and more bytes besides (one tile
+// each, the costliest b -> the cheapest: 7363 x 4096 x 1607 44.8 -> 34.3 us, with 8-bit codes 74.7 -> 52.7; 20000 x 4096 x 768
+// 68.9 -> 37.8, 129.0 -> 58.1).  Except with 8-bit codes, whose tiles take the matrix cores twice as long for less than twice
+// the bytes, and shares of up to three strips, where a second tile weighs most: one band, the fewest runs (768 x 4096 x 16384
+// 55.3 us with the cheapest, 52.0 with one; 1358 x 4096 x 5401 48.3 and 43.3; 6144 x 4096 x 2048 50.8 and 47.2; shares of four,
+// 1412 x 4096 x 10761: 64.1 and 65.6; 4-bit 768 x 4096 x 16384: 34.9 and 36.9).
+inline void choose_bands(TilePlan& pl, int M, int N, bool a8) {
     const long strips = (long)pl.tiles_m * pl.strips_n;
     const long per_worker = (strips + pl.workers - 1) / pl.workers;
     const long rounds = per_worker > 4 ? (per_worker + 3) / 4 : 1;
     double cost[4], limit = 1e300;
     for (int i = 0; i < 4; ++i) cost[i] = (1 << i) <= pl.strips_n ? (double)(rounds << i) * M + (8.0 / (1 << i)) * N : 1e300;
-    for (int tries = 0, first = 0; tries < 4; ++tries) {
+    int first = 0;
+    for (int tries = 0; tries < 4; ++tries) {
         int best = 0;
         for (int i = 1; i < 4; ++i)
             if (cost[i] < cost[best]) best = i;
-        if (cost[best] >= limit) {                     // no better one: the cheapest after all
-            pl.bands = 1 << first;
-            pl.whole_runs = 0;
-            return;
-        }
+        if (cost[best] >= limit) break;
         pl.bands = 1 << best;
         const int ends = run_ends(pl);
         pl.whole_runs = ends == 1;
@@ -247,9 +250,9 @@ inline void choose_bands(TilePlan& pl, int M, int N) {
         }
         cost[best] = 1e300;
     }
+    pl.bands = a8 && per_worker <= 3 ? 1 : 1 << first;
     pl.whole_runs = 0;
 }
-
 
 // K parts wanted for a plan without them: fewer strips than half the workgroups (few rows, narrow N) and a
 // long K.  A part keeps at least 12 K groups: below that the partial sums' round trip costs more than the
@@ -263,8 +266,9 @@ inline int choose_ksplit(const TilePlan& pl, size_t part_bytes, size_t scratch_b
     return ksplit < 1 ? 1 : ksplit;
 }
 
-// Plan of a launch without K parts (ksplit = 1); `glu`: gated output, tiles an even number of strips wide.
-inline TilePlan make_plan(int M, int N, int nb, int cus, bool glu) {
+// Plan of a launch without K parts (ksplit = 1); `glu`: gated output, tiles an even number of strips wide; `a8`: 8-bit
+// activation codes.
+inline TilePlan make_plan(int M, int N, int nb, int cus, bool glu, bool a8) {
     TilePlan pl;
     pl.pair = glu ? 2 : 1;
     pl.tiles_m = (M + kTile - 1) / kTile;
@@ -274,7 +278,7 @@ inline TilePlan make_plan(int M, int N, int nb, int cus, bool glu) {
     pl.ksplit = 1;
     pl.groups = (nb + 7) / 8;
     pl.whole_runs = 0;
-    choose_bands(pl, M, N);
+    choose_bands(pl, M, N, a8);
     return pl;
 }
 

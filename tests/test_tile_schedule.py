@@ -12,11 +12,12 @@ def lib():
     return binding.lib
 
 
-def _schedule(lib, M, N, K, cus, glu, ksplit):
-    n = lib.batq_debug_tile_schedule(M, N, K, cus, int(glu), int(ksplit), None, 0)
+def _schedule(lib, M, N, K, cus, glu, ksplit, a8=False):
+    mode = int(glu) + 2 * int(a8)
+    n = lib.batq_debug_tile_schedule(M, N, K, cus, mode, int(ksplit), None, 0)
     assert n > 0
     buf = (C.c_int * (7 * n))()
-    assert lib.batq_debug_tile_schedule(M, N, K, cus, int(glu), int(ksplit), buf, n) == n
+    assert lib.batq_debug_tile_schedule(M, N, K, cus, mode, int(ksplit), buf, n) == n
     return np.frombuffer(buf, dtype=np.int32).reshape(n, 7).copy()
 
 
@@ -146,3 +147,44 @@ def test_no_share_reaches_into_the_next_run(lib, M, N, glu):
     assert units % 256 and units > 256
     most = -(-(units // 256 + 1) // (2 if glu else 4))
     assert np.bincount(t[:, 0]).max() == most
+
+
+def _bands(t):
+    """Column bands of a schedule: in share order the row panels of one band follow those of the one before."""
+    share = (t[:, 0] % 8) * (256 // 8) + t[:, 0] // 8
+    m0 = t[np.argsort(share, kind="stable"), 1]
+    return 1 + int(np.sum(np.diff(m0) < 0))
+
+
+def _band_bytes(M, N, glu):
+    """Bytes the L2s pull with 1, 2, 4 and 8 bands, in the model of the work split: rounds x bands x M + 8 / bands x N."""
+    units = -(-M // 256) * -(-N // (128 if glu else 64))
+    per = -(-units // 256)
+    rounds = -(-per // 4) if per > 4 else 1
+    return {b: rounds * b * M + 8 / b * N for b in (1, 2, 4, 8) if b <= -(-N // (128 if glu else 64))}, per
+
+
+def test_fewest_bytes_where_every_band_count_leaves_costly_shares(lib):
+    """Where no band count keeps the shares inside their runs, more (or wider) bands only move more bytes: the cheapest count
+    serves; with 8-bit codes and shares of up to three strips a single band, which has the fewest runs."""
+    rng = np.random.default_rng(11)
+    shapes = [(765, 16344, False), (768, 16384, False), (1536, 8192, False), (3072, 4096, False), (6144, 2048, False),
+              (2393, 6458, False), (7363, 1607, False), (2446, 12928, True), (16500, 896, False), (20000, 512, False),
+              (20000, 768, False), (32768, 512, False)]
+    for _ in range(600):
+        glu = bool(rng.integers(0, 4) == 0)
+        shapes.append((int(np.exp(rng.uniform(np.log(300), np.log(20000)))),
+                       64 * int(np.exp(rng.uniform(np.log(8), np.log(300)))) - (0 if glu else int(rng.integers(0, 64))), glu))
+    hit = {False: 0, True: 0}
+    for M, N, glu in shapes:
+        cost, per = _band_bytes(M, N, glu)
+        if -(-M // 256) * -(-N // (128 if glu else 64)) <= 256:
+            continue                                        # a strip or less per workgroup: no share has two
+        for a8 in (False, True):
+            t = _schedule(lib, M, N, 4096, 256, glu, False, a8)
+            if np.bincount(t[:, 0]).max() <= -(-per // (2 if glu else 4)):
+                continue                                    # no share takes more tiles than the largest alone needs
+            bands, least = _bands(t), min(cost.values())
+            hit[a8] += 1
+            assert cost[bands] == least or (a8 and per <= 3 and bands == 1), (M, N, glu, a8, bands, cost)
+    assert hit[False] >= 50 and hit[True] >= 50, hit
