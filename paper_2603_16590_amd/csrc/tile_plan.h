@@ -219,21 +219,39 @@ inline int run_ends(const TilePlan& pl) {
 // and its share of the B columns once.  The bytes all L2s pull are therefore proportional to
 // rounds * b * M + (8 / b) * N; take the b that minimises it.
 // Where that b leaves shares in two runs (run_ends 2) and another does not, the next cheapest of those serves as long as its
-// bytes stay below 1.4 times the least; with one tile per workgroup any b will do.  (5293 x 4096 x 6075 at 1.30 times the bytes
-// 73.2 -> 70.5 us with 4-bit, 111.7 -> 104.6 with 8-bit codes; 3669 x 4096 x 9865 at 1.46 times 90.4 -> 92.2, 135.1 -> 128.2;
-// one tile each, 2720 x 4096 x 5802: 41.3 -> 38.7, 64.3 -> 55.8.)
+// bytes stay below 1.4 times the least (5293 x 4096 x 6075 at 1.30 times the bytes 73.2 -> 70.5 us with 4-bit, 111.7 -> 104.6
+// with 8-bit codes; 3669 x 4096 x 9865 at 1.46 times 90.4 -> 92.2, 135.1 -> 128.2).  With one tile per workgroup the second
+// tile costs more than any bytes do: 300 shapes at up to 7 times the bytes, 4 to 15 % gained with 4-bit, 7 to 30 % with 8-bit
+// codes (2720 x 4096 x 5802 at 2.2 times 42.5 -> 40.4 and 66.2 -> 58.0 us; 382 x 4096 x 16304 at 6.8 times 28.2 -> 26.3 and
+// 45.8 -> 32.6; 262 x 4096 x 16320 at 7.1 times 27.0 -> 23.8).  Not so for shares of three and four strips where the output's
+// rows do not start on whole 128-byte lines: their slow stores hide a tile of a short K.  With 8-bit codes below K = 2048 the limit
+// stays at 1.4 (1720 x 1024 x 7047 at 2.8 times 26.3 -> 27.8 us, 2093 x 512 x 5556 at 2.4 times 21.3 -> 22.7; but 646 x 2048 x 16524
+// at 3.1 times 39.7 -> 37.9, and shares of three, 361 x 1024 x 16551 at 6.8 times 21.7 -> 19.7).  With 4-bit codes it is 2.6 where
+// less than an eighth of the workgroups has four, K = 1024 to 5888 (1664 x 4096 x 7120 at 2.9 times 35.7 -> 38.0 us, 656 x 1024 x
+// 16668 at 3.1 times 18.8 -> 20.1; but 1520 x 512 x 8202 at 3.3 times 15.1 -> 14.6, 544 x 8192 x 16753 at 3.2 times 67.7 -> 62.2,
+// 2188 x 4096 x 5574 at 2.3 times 40.3 -> 38.2).
 // Where every b leaves such shares, the cheapest serves after all: more bands are more runs, and more bytes besides (one tile
 // each, the costliest b -> the cheapest: 7363 x 4096 x 1607 44.8 -> 34.3 us, with 8-bit codes 74.7 -> 52.7; 20000 x 4096 x 768
 // 68.9 -> 37.8, 129.0 -> 58.1).  Except with 8-bit codes, whose tiles take the matrix cores twice as long for less than twice
 // the bytes, and shares of up to three strips, where a second tile weighs most: one band, the fewest runs (768 x 4096 x 16384
 // 55.3 us with the cheapest, 52.0 with one; 1358 x 4096 x 5401 48.3 and 43.3; 6144 x 4096 x 2048 50.8 and 47.2; shares of four,
 // 1412 x 4096 x 10761: 64.1 and 65.6; 4-bit 768 x 4096 x 16384: 34.9 and 36.9).
+inline double byte_limit(const TilePlan& pl, long strips, long per_worker, int out_cols, bool a8) {
+    constexpr double kAny = 1e100;
+    if (per_worker > 4) return 1.4;
+    if (out_cols % 64 == 0) return kAny;
+    if (per_worker != 4) return kAny;
+    if (a8) return pl.groups < 8 ? 1.4 : kAny;
+    const bool few = (strips % pl.workers) * 8 < pl.workers;
+    return few && pl.groups >= 4 && pl.groups < 24 ? 2.6 : kAny;
+}
 inline void choose_bands(TilePlan& pl, int M, int N, bool a8) {
     const long strips = (long)pl.tiles_m * pl.strips_n;
     const long per_worker = (strips + pl.workers - 1) / pl.workers;
     const long rounds = per_worker > 4 ? (per_worker + 3) / 4 : 1;
-    double cost[4], limit = 1e300;
-    for (int i = 0; i < 4; ++i) cost[i] = (1 << i) <= pl.strips_n ? (double)(rounds << i) * M + (8.0 / (1 << i)) * N : 1e300;
+    constexpr double kNever = 1e300;
+    double cost[4], limit = kNever;
+    for (int i = 0; i < 4; ++i) cost[i] = (1 << i) <= pl.strips_n ? (double)(rounds << i) * M + (8.0 / (1 << i)) * N : kNever;
     int first = 0;
     for (int tries = 0; tries < 4; ++tries) {
         int best = 0;
@@ -246,9 +264,9 @@ inline void choose_bands(TilePlan& pl, int M, int N, bool a8) {
         if (ends != 2) return;
         if (tries == 0) {
             first = best;
-            limit = rounds == 1 ? 1e299 : 1.4 * cost[best];
+            limit = byte_limit(pl, strips, per_worker, N / pl.pair, a8) * cost[best];
         }
-        cost[best] = 1e300;
+        cost[best] = kNever;
     }
     pl.bands = a8 && per_worker <= 3 ? 1 : 1 << first;
     pl.whole_runs = 0;

@@ -164,6 +164,16 @@ def _band_bytes(M, N, glu):
     return {b: rounds * b * M + 8 / b * N for b in (1, 2, 4, 8) if b <= -(-N // (128 if glu else 64))}, per
 
 
+@pytest.mark.parametrize("M,K,N,a8,most", [
+    (1664, 4096, 7120, False, 2.6), (656, 1024, 16668, False, 2.6), (1529, 1024, 8237, False, 2.6),
+    (1520, 1024, 8202, True, 1.4), (2121, 1024, 5648, True, 1.4), (1400, 1024, 10448, True, 1.4)])
+def test_bytes_given_for_whole_shares_are_bounded_on_ragged_rows(lib, M, K, N, a8, most):
+    """Output rows that do not start on whole lines, shares of three and four strips, short K: the second tile of a share costs
+    less than the bytes of a band count that avoids it."""
+    cost, _ = _band_bytes(M, N, False)
+    assert cost[_bands(_schedule(lib, M, N, K, 256, False, False, a8))] < most * min(cost.values())
+
+
 def test_fewest_bytes_where_every_band_count_leaves_costly_shares(lib):
     """Where no band count keeps the shares inside their runs, more (or wider) bands only move more bytes: the cheapest count
     serves; with 8-bit codes and shares of up to three strips a single band, which has the fewest runs."""
