@@ -348,9 +348,10 @@ batq_status batq_linear_glu(const batq_transform* t, const batq_weight* w, const
  *
  * batq_dequantize: codes (DEVICE, device order of the given width) and scales (DEVICE, grouped order) of `M`
  *   rows -> out[m][j] = value(code) * 2^(scale - 127), row-major with row stride ldo elements (16-byte aligned
- *   rows), bf16 or fp32.  fp32 output is exact (subnormal results included; scale byte 255 and the E4M3 NaN
- *   codes give NaN); bf16 output uses the hardware's scaled converts and is exact for every result in bf16's
- *   normal range (results below 2^-126 are not specified).  bits = 4 or 8, else BATQ_ERR_UNSUPPORTED.
+ *   rows), bf16 or fp32.  codes must be 16-byte aligned; scales may start at any byte.  fp32 output is exact
+ *   (subnormal results included; scale byte 255 and the E4M3 NaN codes give NaN); bf16 output uses the hardware's
+ *   scaled converts and is exact for every result in bf16's normal range (results below 2^-126 are not specified).
+ *   bits = 4 or 8, else BATQ_ERR_UNSUPPORTED.
  *
  * batq_transform_apply: out = X T_k (FORWARD), X T_k^-1 (INVERSE) or X T_k^-T (INVERSE_T) block by block, no
  *   clipping or quantisation.  bf16 input with 16-byte aligned X, out and row pitches runs on the matrix

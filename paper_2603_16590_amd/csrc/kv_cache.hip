@@ -108,7 +108,7 @@ dequant_kernel(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ sc
 #pragma unroll
     for (int i = 0; i < kSub; ++i) {
         const int row = min(max(rg * 16 + i * kRows + lr, row0), row0 + M - 1);
-        sw[i] = *reinterpret_cast<const uint64_t*>(scales + ((size_t)g * srows + row) * 8);
+        __builtin_memcpy(&sw[i], scales + ((size_t)g * srows + row) * 8, 8);   // (scales may start at any byte)
     }
 #pragma unroll
     for (int i = 0; i < kSub; ++i) {

@@ -320,3 +320,23 @@ def test_window_edges_of_the_dequantiser(B, bits, K):
             torch.cuda.synchronize()
             assert torch.equal(wide[:m, :K], ref[row0:row0 + m]), (row0, m)
             assert bool((wide[:, K:] == 7.0).all()) and bool((wide[m:] == 7.0).all()), (row0, m)
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("offset", [1, 2, 4, 7])
+def test_dequantiser_takes_scales_at_any_byte(B, bits, offset):
+    """The scales of a window may be a view into a packed buffer that starts at any byte: the values of an aligned copy."""
+    import torch
+    cap, K = 75, 288
+    gen = torch.Generator(device="cuda").manual_seed(bits)
+    n = B.batq_code8_bytes(cap, K) if bits == 8 else B.batq_code_bytes(cap, K)
+    codes = torch.randint(0, 120, (n,), dtype=torch.uint8, device="cuda", generator=gen)
+    scales = torch.randint(120, 135, (B.batq_scale_bytes(cap, K),), dtype=torch.uint8, device="cuda", generator=gen)
+    packed = torch.zeros(scales.numel() + 16, dtype=torch.uint8, device="cuda")
+    view = packed[offset:offset + scales.numel()]
+    view.copy_(scales)
+    for dtype in (torch.bfloat16, torch.float32):
+        ref = B.batq_kv_dequantize(codes, scales, cap, 5, 66, K, bits, out_dtype=dtype)
+        got = B.batq_kv_dequantize(codes, view, cap, 5, 66, K, bits, out_dtype=dtype)
+        torch.cuda.synchronize()
+        assert torch.equal(got, ref)
