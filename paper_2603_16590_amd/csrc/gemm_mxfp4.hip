@@ -1762,8 +1762,12 @@ inline GemmPlan gemm_plan(int M, int N, int nb, int cus, bool a8, bool glu, size
         auto even_unit = [&](int most) {
             const int rounds = (n_out + most * cus - 1) / (most * cus);
             // K with fewer groups than a workgroup has waves: launch-bound, more workgroups only read X more often
-            // (gated 30 x 1024 x 2 x 6400 4.18 us with units of 32, 4.30 with 28)
-            if (rounds == 1 && n_out > 16 * cus && scale_groups(nb) < kSkinnyWaves) return most;
+            // (gated 30 x 1024 x 2 x 6400 4.18 us with units of 32, 4.30 with 28), in later rounds of units of 32 as well
+            // (32 x 1024 x 12288 4.09, 4.26 with 24; 32 x 1024 x 18944 5.43, 5.81 with 28; 32 x 256 x 18944 4.30, 4.68), and
+            // with one or two groups where units of 16 would make one round (gated 16 x 256 x 2 x 4096 2.93, 3.02 with 16;
+            // but four groups, 16 x 1024 x 2 x 2048: 3.75, 3.62 with 16)
+            const int least = glu && scale_groups(nb) < 3 ? 0 : 16 * cus;
+            if ((rounds == 1 || most == 32) && n_out > least && scale_groups(nb) < kSkinnyWaves) return most;
             return std::max(16, ((n_out + rounds * cus - 1) / (rounds * cus) + 3) & ~3);
         };
         g.unit = even_unit(32);

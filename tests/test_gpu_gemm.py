@@ -361,10 +361,10 @@ def test_weight_codes_of_two_gib(B):
 
 
 @pytest.mark.parametrize("M,K,N", [(3, 2080, 5000), (1, 2080, 8196), (16, 288, 14336), (17, 2080, 14336), (32, 64, 18944 + 5),
-                                   (8, 2304, 8200)])
+                                   (8, 2304, 8200), (16, 2080, 14336), (2, 2080, 18944 + 5)])
 def test_small_m_even_units(B, M, K, N):
     """Up to 32 rows the columns are cut into equal units for the compute units: 20 columns, 36 and 56 as two matrix
-    tiles, 28, and a third round of workgroups; ragged last units."""
+    tiles, 28, and a third round of workgroups; ragged last units; whole units of 32 where K is short."""
     test_small_shapes_random_codes(B, M, K, N)
 
 

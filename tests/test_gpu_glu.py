@@ -147,8 +147,10 @@ def test_gemm_glu_few_row_kernel(B, M, K, F, bits):
     test_gemm_glu_random_codes(B, M, K, F, bits)
 
 
-# up to 32 rows: units of 20, 28 and (second round) 20 outputs, units that cross a group of 32 gate columns, a ragged last unit
-@pytest.mark.parametrize("M,K,F", [(2, 2080, 4128 + 32), (32, 288, 14336), (7, 64, 9664)])
+# up to 32 rows: units of 20, 28 and (second round) 20 outputs, units that cross a group of 32 gate columns, a ragged last unit;
+# whole units of 32 where K is short
+@pytest.mark.parametrize("M,K,F", [(2, 2080, 4128 + 32), (32, 288, 14336), (7, 64, 9664), (32, 2080, 14336), (7, 2080, 9664),
+                                   (5, 512, 96), (5, 544, 96)])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_gemm_glu_small_m_even_units(B, M, K, F, bits):
     test_gemm_glu_random_codes(B, M, K, F, bits)
