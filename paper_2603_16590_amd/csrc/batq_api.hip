@@ -241,6 +241,9 @@ batq_status batq_transform_create_ex(batq_transform** out, const batq_transform_
     std::vector<uint16_t> Tsplit, TinvSplit, TinvTSplit;
     if (form != BATQ_FORM_IDENTITY) {
         T.resize((size_t)nb * 1024);
+        if (form == BATQ_FORM_KRON)                          // (with room for the inverted factors behind the blocks)
+            Tinv.reserve((size_t)nb * 1024 + (size_t)(d->outer_per_block ? nb : 1) * go * go +
+                         (size_t)(d->inner_per_block ? nb : 1) * gi * gi);
         Tinv.resize((size_t)nb * 1024);
         if (form == BATQ_FORM_KRON) {
             std::vector<double> Od(go * go), Oinv(go * go), Id(gi * gi), Iinv(gi * gi);
