@@ -368,10 +368,12 @@ def test_small_m_even_units(B, M, K, N):
     test_small_shapes_random_codes(B, M, K, N)
 
 
-@pytest.mark.parametrize("M,K,N", [(333, 96, 5000), (2000, 64, 700), (129, 64, 4040), (300, 6144, 1984 - 5), (1030, 96, 640 - 3)])
+@pytest.mark.parametrize("M,K,N", [(333, 96, 5000), (2000, 64, 700), (129, 64, 4040), (300, 6144, 1984 - 5), (1030, 96, 640 - 3),
+                                   (129, 64, 4000), (1900, 96, 640 - 3), (1024, 6144, 576)])
 def test_few_row_kernel_tile_orders(B, M, K, N):
-    """Several row panels and a number of strips that is no multiple of 8: an XCD takes every eighth strip or every
-    eighth panel, with and without K parts, one missing of the last eight.  (Element by element: with only 64 to 96
+    """Several row panels: an XCD takes every eighth strip (79, 31 with K parts, and 63 strips) or every eighth panel (16, 15, and
+    8 with K parts), one missing of the last eight or none; a multiple of 8 strips and 9 panels by 10 strips stay in the plain
+    order.  (Element by element: with only 64 to 96
     products a sum of random codes is often a bf16 tie, which a last-bit difference of the fp32 sum turns by one bf16
     unit, up to 2^-8; a tie in 12 sums is already 2^-8 / sqrt(12) = 1.1e-3 in the Frobenius norm of all of them.)"""
     test_split_k_shapes(B, M, K, N) if K >= 6144 else _check_every_element(B, M, K, N)

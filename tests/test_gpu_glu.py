@@ -139,9 +139,10 @@ def test_linear_glu_is_quantise_then_gemm_glu_and_errors(B):
     assert bool((Hz == 0).all())
 
 
-# the few-row kernel with gated output: 33..64 rows with 16 K groups and 65 strips, pairs of strips (odd number of strips), wave edges
+# the few-row kernel with gated output: 33..64 rows with 16 K groups and 65 strips, pairs of strips (odd number of strips), wave edges,
+# an XCD's every eighth panel
 @pytest.mark.parametrize("M,K,F", [(33, 4096, 2080), (64, 4096 + 32, 224), (40, 64, 8192 + 32), (97, 352, 160), (129, 96, 4128),
-                                   (200, 288, 7200)])
+                                   (200, 288, 7200), (1900, 96, 320)])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_gemm_glu_few_row_kernel(B, M, K, F, bits):
     test_gemm_glu_random_codes(B, M, K, F, bits)

@@ -274,7 +274,8 @@ def test_a8w4_linear_configs(B, cfg):
 # the few-row kernel with 8-bit activations: wave and panel edges, one strip and (odd) pairs of strips per workgroup, a ragged
 # last strip, 2 to 50 stages, K parts; 33 rows by N > 8192 is where it takes over from the small-M kernel
 @pytest.mark.parametrize("M,K,N", [(33, 96, 8200), (64, 288, 14336), (65, 32, 64), (127, 224, 70), (129, 1600, 200),
-                                   (200, 288, 14400 - 7), (1000, 544, 3000), (100, 12288 + 32, 3000)])
+                                   (200, 288, 14400 - 7), (1000, 544, 3000), (100, 12288 + 32, 3000),
+                                   (1900, 96, 640 - 3), (1024, 8192, 576)])         # an XCD's every eighth panel, K parts
 def test_a8w4_few_row_kernel(B, M, K, N):
     test_a8w4_tile_schedule_shapes(B, M, K, N)
 

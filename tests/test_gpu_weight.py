@@ -87,12 +87,23 @@ def test_layouts_clip_and_dtypes(B):
     assert np.array_equal(gc, oc) and np.array_equal(gs, os_)
 
 
+def _leave_other_bytes(B, K, N):
+    """Frees blocks of the size a K x N weight takes, full of codes and scales that a product would show: the allocator hands
+    a freed block out again.  Their valid region covers the weight's padding (K up to 256, N up to 32)."""
+    import torch
+    Kp, Np = -(-K // 256) * 256, -(-N // 32) * 32
+    codes = torch.full((Np, Kp // 2), 0x77, dtype=torch.uint8, device="cuda")
+    scales = torch.full((Np, Kp // 32), 0xFF, dtype=torch.uint8, device="cuda")
+    for w in [B.batq_weight_import(codes, scales, Kp, Np) for _ in range(3)]:
+        w.close()
+
+
 @pytest.mark.parametrize("form", ["kron4", "kron8", "dense", "identity"])
 @pytest.mark.parametrize("K,N", [(32, 1), (96, 33), (288, 257)])
 def test_forms_storages_and_padding(B, form, K, N):
     """Every form from both storages (16-byte aligned rows or not) on edges of the kernel's tiles, and the padding it
-    writes: a product with the weight reads whole K groups and row groups, so leftovers of the previous owner of the
-    memory would show in it."""
+    writes: a product with the weight reads whole K groups, so leftovers of the previous owner of the memory would show
+    in it (scale 255 as a NaN, codes because the activation's padding holds ones here)."""
     import torch
     rng = np.random.default_rng(K + N)
     nb = K // 32
@@ -113,7 +124,16 @@ def test_forms_storages_and_padding(B, form, K, N):
     X = torch.from_numpy(rng.standard_normal((3, K)).astype(np.float32)).cuda()
     xc, xs = B.batq_quantize_act(B.Transform(K, None, None, None), X)
     rmx = B.batq_codes_to_rowmajor(xc, 3, K).cpu().numpy(), B.batq_scales_to_rowmajor(xs, 3, K).cpu().numpy()
-    junk = torch.full((64, K), 0xEE, dtype=torch.uint8, device="cuda")
+    for row in range(3):
+        for k in range(nb, -(-nb // 8) * 8):
+            at = B.lib.batq_code_chunk_offset(row, k, K)
+            xc[at:at + 16] = 0x22
+    # what the leftovers would do to a product
+    Kp = -(-K // 256) * 256
+    left = B.batq_weight_import(torch.full((32, Kp // 2), 0x77, dtype=torch.uint8, device="cuda"),
+                                torch.full((32, Kp // 32), 0xFF, dtype=torch.uint8, device="cuda"), Kp, 32)
+    assert not bool(torch.isfinite(B.batq_gemm_mxfp4(xc, xs, left, 3)).any())
+    left.close()
     for dtype in (torch.float32, torch.bfloat16):
         Wd = torch.from_numpy(W).cuda().to(dtype)
         pitch = (N + 15) // 8 * 8 + 1                                   # odd row pitch
@@ -122,9 +142,7 @@ def test_forms_storages_and_padding(B, form, K, N):
         tall = torch.zeros((N, K + 1), dtype=dtype, device="cuda")      # rows that are not 16-byte aligned
         tall[:, :K] = Wd.t()
         for M_, kxn in ((Wd, True), (wide[:, :N], True), (Wd.t().contiguous(), False), (tall[:, :K], False)):
-            # the allocator hands a freed block out again: fill one of about this size with other bytes first
-            B.batq_weight_import(junk.repeat((N + 63) // 64, 1)[:N, :K // 2].contiguous(),
-                                 junk.repeat((N + 63) // 64, 1)[:N, :nb].contiguous(), K, N).close()
+            _leave_other_bytes(B, K, N)
             if M_.stride(0) < M_.shape[1] or M_.stride(1) != 1:          # (a single column or row loses its pitch)
                 continue
             wh = B.batq_prepare_weight(t, M_, kxn)
