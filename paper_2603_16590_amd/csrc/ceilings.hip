@@ -1,8 +1,8 @@
 // batq_ceilings: measures, on the GPU it runs on, the practical ceilings that the two hot
 // kernels of libbatq are judged against, next to the data-sheet peaks:
-//   - the block-scaled FP4 matrix instruction issued back to back from registers (no memory
-//     traffic at all), with constant and with random operand bits: the matrix pipe is
-//     power-limited, so the sustainable rate depends on how many operand bits toggle;
+//   - the block-scaled matrix instruction issued back to back from registers (no memory
+//     traffic at all), FP4 x FP4 and FP8 x FP4, with constant and with random operand bits: the matrix
+//     pipe is power-limited, so the sustainable rate depends on how many operand bits toggle;
 //   - streaming HBM reads, a plain copy, and a read:write mix in the ratio of the activation
 //     quantiser (2 bytes in, 0.53 bytes out per element), over buffers larger than the
 //     last-level cache.
@@ -28,6 +28,8 @@ typedef float v16f __attribute__((ext_vector_type(16)));
     } while (0)
 
 // 16 independent accumulators per wave, one wave per SIMD: the shape of the GEMM's inner loop.
+// FORMAT of the first operand: 4 FP4 (E2M1), 0 FP8 (E4M3); the second one is FP4.
+template <int FORMAT>
 __global__ void __launch_bounds__(256, 1)
 mfma_loop(const v8i* __restrict__ a, const v8i* __restrict__ b, v16f* __restrict__ sink, int iters) {
     const int t = threadIdx.x & 63;
@@ -38,7 +40,7 @@ mfma_loop(const v8i* __restrict__ a, const v8i* __restrict__ b, v16f* __restrict
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, acc[i], 4, 4, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
+            acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, acc[i], FORMAT, 4, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
     }
     float s = 0.f;
 #pragma unroll
@@ -99,28 +101,31 @@ int main() {
     CK(hipMalloc(&da, 64 * 32));
     CK(hipMalloc(&db, 64 * 32));
     CK(hipMalloc(&dsink, 4096));
-    double mfma_tflops[2];
+    double mfma_tflops[2], mfma8_tflops[2];
     const int blocks = prop.multiProcessorCount, iters = 4000;
+    auto rate = [&](auto kernel) {
+        kernel<<<blocks, 256>>>(da, db, dsink, 50);
+        CK(hipDeviceSynchronize());
+        CK(hipEventRecord(e0));
+        kernel<<<blocks, 256>>>(da, db, dsink, iters);
+        CK(hipEventRecord(e1));
+        return (double)blocks * 4 * iters * 16 * 2.0 * 32 * 32 * 64 / elapsed_ms() / 1e9;
+    };
     for (int pat = 0; pat < 2; ++pat) {
         std::vector<uint32_t> h(512);
         uint32_t lcg = 12345u;
-        for (auto& x : h) {
-            lcg = lcg * 1664525u + 1013904223u;
-            x = pat == 0 ? 0x22222222u : lcg;
-        }
-        CK(hipMemcpy(da, h.data(), 2048, hipMemcpyHostToDevice));
-        for (auto& x : h) {
-            lcg = lcg * 1664525u + 1013904223u;
-            x = pat == 0 ? 0x22222222u : lcg;
-        }
-        CK(hipMemcpy(db, h.data(), 2048, hipMemcpyHostToDevice));
-        mfma_loop<<<blocks, 256>>>(da, db, dsink, 50);
-        CK(hipDeviceSynchronize());
-        CK(hipEventRecord(e0));
-        mfma_loop<<<blocks, 256>>>(da, db, dsink, iters);
-        CK(hipEventRecord(e1));
-        const double ms = elapsed_ms();
-        mfma_tflops[pat] = (double)blocks * 4 * iters * 16 * 2.0 * 32 * 32 * 64 / ms / 1e9;
+        auto fill = [&](v8i* dst, uint32_t keep) {
+            for (auto& x : h) {
+                lcg = lcg * 1664525u + 1013904223u;
+                x = pat == 0 ? 0x22222222u : lcg & keep;
+            }
+            CK(hipMemcpy(dst, h.data(), 2048, hipMemcpyHostToDevice));
+        };
+        fill(da, ~0u);
+        fill(db, ~0u);
+        mfma_tflops[pat] = rate(mfma_loop<4>);
+        fill(da, 0xBFBFBFBFu);                      // E4M3 codes below 2 (no NaN among them)
+        mfma8_tflops[pat] = rate(mfma_loop<0>);
     }
 
     // ---- memory: six buffer pairs of 112 MiB in, 28 MiB + 1.75 MiB out (> 2x the 256 MB cache)
@@ -152,9 +157,11 @@ int main() {
 
     printf("{\"device\": \"%s\", \"compute_units\": %d, "
            "\"mfma_fp4_32x32x64_tflops_const_operands\": %.0f, \"mfma_fp4_32x32x64_tflops_random_operands\": %.0f, "
+           "\"mfma_fp8xfp4_32x32x64_tflops_const_operands\": %.0f, \"mfma_fp8xfp4_32x32x64_tflops_random_operands\": %.0f, "
            "\"hbm_stream_read_gbs\": %.0f, \"hbm_copy_gbs\": %.0f, \"copy_bytes_each_way\": %zu, "
            "\"hbm_quant_mix_gbs\": %.0f}\n",
-           prop.gcnArchName, prop.multiProcessorCount, mfma_tflops[0], mfma_tflops[1], rbytes / ms_read / 1e6,
+           prop.gcnArchName, prop.multiProcessorCount, mfma_tflops[0], mfma_tflops[1], mfma8_tflops[0],
+           mfma8_tflops[1], rbytes / ms_read / 1e6,
            2.0 * rbytes / ms_copy / 1e6, rbytes, mix_bytes / ms_mix / 1e6);
     return 0;
 }
