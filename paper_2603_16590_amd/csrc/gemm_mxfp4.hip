@@ -1192,8 +1192,8 @@ __device__ __forceinline__ void mid_steps(MidCtx<RT, D, NS, A8>& c, int base, co
 // 15.8 -> 14.1 (18.9 -> 16.9).
 enum MidOrder { kMidPlain = 0, kMidByStrip = 1, kMidByPanel = 2 };
 
-// Requires operand code arrays below 2 GiB (32-bit load offsets).  Grid: see MidOrder; YT = partial_f32: partial sums of K part blockIdx.z in store_partial order (ldy = 32-column blocks of the
-// padded output, part_stride = floats of a part).
+// Requires operand code arrays below 2 GiB (32-bit load offsets).  Grid: see MidOrder.  YT = partial_f32: partial sums of the
+// workgroup's K part in store_partial order (ldy = 32-column blocks of the padded output, part_stride = floats of a part).
 template <typename YT, int RT, int D, int NS, bool A8, bool GLU>
 __global__ void __launch_bounds__(256, A8 && NS == 2 ? 1 : 2)
 gemm_mid(const uint8_t* __restrict__ xc, const uint8_t* __restrict__ xs, const uint8_t* __restrict__ wc,
@@ -1732,7 +1732,9 @@ inline GemmPlan gemm_plan(int M, int N, int nb, int cus, bool a8, bool glu, size
         // 64 x 4096 x 8192 10.7 -> 13.9).  Gated: the same, and where K has at least 16 groups and a quarter of the compute
         // units a workgroup (64 x 4096 x 2 x 4096 11.4 -> 10.3 us, 48 x 8192 x 2 x 2048 17.0 -> 15.7, 64 x 4096 x 2 x 14336
         // 22.9 -> 17.6; but 48 x 2048 x 2 x 4096 5.9 -> 6.4, 64 x 4096 x 2 x 1024 8.4 -> 9.1); 8-bit gated always
-        // (48 x 2048 x 2 x 4096 10.9 -> 8.4 us, 64 x 4096 x 2 x 14336 47.3 -> 21.6).
+        // (48 x 2048 x 2 x 4096 10.9 -> 8.4 us, 64 x 4096 x 2 x 14336 47.3 -> 21.6).  One chain of sums over K instead of eight is as
+        // close to fp64 sums of the same codes: relative error, eight -> one, 8-bit 64 x 14336 x 14336 1.577e-5 -> 1.578e-5, gated
+        // 64 x 4096 x 2 x 14336 2.744e-5 both, 4-bit gated 48 x 14336 x 2 x 4096 5.34e-8 both (8-bit: the instruction's own window).
         if (M <= 64 && g.mid) {
             const int cols = (N + (glu ? 63 : 31)) / (glu ? 64 : 32);       // the small-M kernel's workgroups
             if (glu) g.mid = a8 || cols > cus || (scale_groups(nb) >= 16 && 4 * cols >= cus);

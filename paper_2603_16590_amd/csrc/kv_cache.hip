@@ -69,8 +69,10 @@ __device__ __forceinline__ void store8<uint16_t>(uint16_t* p, const float (&v)[8
 // 256 (512) contiguous code bytes and writes 4 (8) rows x 256 (128) contiguous output bytes.  All codes of the unit and
 // the 8-byte scale words of its rows are requested before the first conversion: a scale byte fetched inside the window's
 // bounds check is a load the compiler has to wait for, one after the other, sixteen of them in units of 32 rows
-// (graph-replayed, 8-bit codes to bf16: 1024 x 1024 7.5 -> 3.9 us, 8192 x 1024 10.8 -> 8.0, 32768 x 1024 27.4 ->
-// 22.3; 4-bit 8192 x 1024 9.8 -> 6.6).  Rows outside the window take the scales of the nearest row inside and are not stored.
+// (graph-replayed, windows taking turns beyond the memory-side cache, 8-bit codes to bf16: 1024 x 1024 7.8 -> 4.2 us, 8192 x 1024
+// 10.5 -> 7.7, 32768 x 1024 27.1 -> 21.7; 4-bit 8192 x 1024 9.9 -> 6.6; one window read over and over, resident in that cache:
+// 8192 x 1024 8.4 -> 5.4, but 32768 x 1024 13.6 -> 15.0).  Units of 32 rows with scale words: 14.0 there, but 8192 x 2048 7.3 ->
+// 11.8 and 1024 x 1024 4.3 -> 5.6.  Rows outside the window take the scales of the nearest row inside and are not stored.
 // bf16 output uses the hardware converts (two codes -> two bf16, times 2^(scale byte - 127)); they are exact for
 // every result in bf16's normal range, smaller ones are not specified here.  fp32 output is computed as
 // code value x 2^(byte - 127), exact in fp32 (subnormals included; scale byte 255 and the E4M3 NaN codes give NaN).
